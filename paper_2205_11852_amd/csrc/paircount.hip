@@ -9,9 +9,10 @@
 // 2^24 in magnitude and exact in float32.
 //
 // Work decomposition: a work item is (task, run of consecutive cells of
-// catalogue a).  Items form eight queues, one per XCD (workgroup w runs on
-// XCD w mod 8), each holding a contiguous, cost-balanced range of tasks so
-// that the blocks sharing an XCD's L2 share catalogues; a block whose queue
+// catalogue a), in small batches a cell's part of the stencil (split_items).
+// Items form eight queues, one per XCD (workgroup w runs on XCD w mod 8),
+// each holding a contiguous, cost-balanced range of items so that the blocks
+// sharing an XCD's L2 share catalogues; a block whose queue
 // is empty moves on to the next queue.  A block takes one item at a time and
 // its waves share the item's stencil offsets.  For each chunk of i points
 // (up to a whole cell of catalogue a, read through wave-uniform scalar
@@ -55,6 +56,7 @@ constexpr int kJ = 128;     // midpoint: rows of the per-wave j table (the swept
 constexpr int kx_for(int los, bool h16) { return los == 1 ? kXm : h16 ? kX16 : kX; }
 constexpr int kx_bytes(int los, bool h16) { return kx_for(los, h16) * (los == 1 ? 32 : 16); }
 constexpr int kXcd = 8;     // queues (one per XCD)
+constexpr int kQStride = 32;  // words between their counters: a 128-byte line each
 
 struct PcParams {
     int32_t n[3];
@@ -69,7 +71,8 @@ struct PcParams {
     int32_t pad1;
     int32_t nhalf, nfull;
     int32_t cells_per_item, items_per_task;
-    int32_t chunk, pad3;        // i points per chunk (multiple of 4, <= 64)
+    int32_t chunk;              // i points per chunk (multiple of 4, at most 256)
+    int32_t nslice;             // items that share one run of cells, each with its part of the stencil
     int32_t n_r, n_mu, nbins;
     int32_t hist_stride;    // uint32 words of the block histogram (bins + a discard slot)
     int32_t queue_byte0;    // LDS byte offset of wave 0's queue
@@ -84,6 +87,7 @@ struct PcParams {
     uint32_t h16_init;          // 16-bit bins: initial value of a histogram word (two bins)
     uint32_t wave_limit;        // candidate tests a wave may register between flushes
     uint32_t qstart[kXcd + 1];  // queue x holds items [qstart[x], qstart[x+1])
+    int32_t qstride;            // words from one queue's counter to the next
 };
 
 typedef unsigned __int128 u128;
@@ -785,22 +789,36 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
     // work items are taken by the whole block (thread 0 pops, the others read
     // the item from LDS), so the block's waves always count the same task
     int xq = int(blockIdx.x % kXcd);
-    int exhausted = 0;
     int cur_task = -1;
     for (;;) {
         __syncthreads();  // the previous item is done everywhere; ctl is free
-        if (threadIdx.x == 0) {
+        if (wid == 0) {
+            // Every counter has a cache line of its own, so the pops of one
+            // XCD's queue stay in its L2.  An empty queue is left by looking
+            // at all eight counters at once, one per lane: eight failing
+            // atomic adds in a row, on lines that every XCD's blocks pull to
+            // and fro, cost 0.1 us a block one after the other (5 tasks of
+            // 3001 points: 170 us of kernel, 63 us this way).
             unsigned it = 0xFFFFFFFFu;
-            while (exhausted < kXcd) {
-                const unsigned v = p.qstart[xq] + atomicAdd(&queue[xq], 1u);
+            for (;;) {
+                unsigned v = 0;
+                if (lane == 0) v = atomicAdd(&queue[xq * p.qstride], 1u);
+                v = p.qstart[xq] + __builtin_amdgcn_readfirstlane(v);
                 if (v < p.qstart[xq + 1]) {
                     it = v;
                     break;
                 }
-                ++exhausted;
-                xq = (xq + 1) % kXcd;
+                bool has = false;
+                if (lane < kXcd)
+                    has = __hip_atomic_load(&queue[lane * p.qstride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                          p.qstart[lane + 1] - p.qstart[lane];
+                const uint32_t left = uint32_t(__builtin_amdgcn_ballot_w64(has));
+                if (!left) break;
+                // the first of them after xq, cyclically
+                const uint32_t after = left & ~((2u << xq) - 1u);
+                xq = __builtin_ctz(after ? after : left);
             }
-            ctl[0] = it;
+            if (lane == 0) ctl[0] = it;
         }
         __syncthreads();
         const unsigned item = __builtin_amdgcn_readfirstlane(ctl[0]);
@@ -835,7 +853,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
         const int2 tk = tasks[task];
         const bool autop = tk.x == tk.y;
         const int64_t abase = int64_t(tk.x) * p.ncell, bbase = int64_t(tk.y) * p.ncell;
-        const int c0 = g * p.cells_per_item;
+        const int slice = g % p.nslice;
+        const int c0 = (g / p.nslice) * p.cells_per_item;
         const int c1 = min(c0 + p.cells_per_item, int(p.ncell));
         const int ns = autop ? p.nhalf : p.nfull;
         const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
@@ -898,7 +917,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                 // first wave, each lane's j index relative to the chunk start
                 // (i indices within the chunk are below 256).
                 if (autop && wid == 0) {
-                    for (int64_t jb = ib + 1; jb < ia1; jb += 64) {
+                    for (int64_t jb = ib + 1 + 64 * slice; jb < ia1; jb += 64 * p.nslice) {
                         const int n = int(min(ia1 - jb, int64_t(64)));
                         const int32_t jo = int32_t(jb - w.b0);
                         const int32_t io = int32_t(jb - ib);
@@ -989,8 +1008,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(6))) void 
                     kfill = 64;
                     return true;
                 };
-                // the block's waves share the stencil offsets of the chunk
-                for (int s = wid; s < ns; s += nwave) {
+                // the waves of the block, and of the items that share this run
+                // of cells, take the stencil offsets of the chunk in turn
+                for (int s = wid + slice * nwave; s < ns; s += nwave * p.nslice) {
                     if (autop && s == 0) continue;  // the i cell itself: above
                     const int4 o = sten[s];
                     int jx = cx + o.x, jy = cy + o.y, jz = cz + o.z;
@@ -1128,7 +1148,8 @@ struct Plan {
     // staged device block layout
     std::vector<unsigned char> blob;
     size_t off_tasks, off_order, off_sten, off_e2, off_otab, off_queue;
-    int n_queue;
+    int n_queue;         // words of the queue counters
+    size_t pad;          // bytes of the block that only space the counters out
 };
 
 static float f32_up(double v) {  // smallest float >= v
@@ -1141,6 +1162,45 @@ static float f32_down(double v) {  // largest float <= v
     float f = float(v);
     if (double(f) > v) f = std::nextafter(f, -INFINITY);
     return f;
+}
+
+// Work items of a persistent launch.  An item is a run of cells of a task's
+// i catalogue, or with slices one cell and every nslice-th part of its
+// stencil.  What bounds small batches is the tail: rows of cells (the first
+// rule, whatever the batch) left 1536 block slots with 100 items for one
+// 1e5-point DD (3.5 ms; 8 slices per cell: 0.45 ms), 800 items for two mocks
+// of 1e5 (7.2 ms; 2 slices: 2.95 ms), 578 dense rows per wedge task (10 mocks
+// of 3e5: 45.6 ms; single cells: 37.2 ms) and left the last round of 1000
+// items per box task half empty (64 mocks of 1e5: 79.0 -> 76.4 ms).  What
+// speaks for larger items is the cost of one: a pop, two barriers and, since
+// consecutive items of a queue go to different blocks, often a flush of the
+// histogram.  So a cell stands alone when its expected candidate tests pay
+// for that (below kRowTests, runs of cells up to a row: (r_p, pi) counts of
+// 3.5e4 tests per cell run 2.67 ms in pairs of cells, 2.75-2.83 ms singly),
+// unless that would leave fewer than two items per slot; and it is cut into
+// slices of at least kSliceTests while there are fewer than eight items per
+// slot.  More than 8 slices gain nothing (the waves' last, partly filled
+// j blocks grow in number: 16 slices of the single DD 0.57 ms).
+constexpr double kRowTests = 1e5, kSliceTests = 5e4;
+
+static void split_items(PcParams& p, const GridGeom& g, const lc_tuning* tune, bool per_task, int n_tasks,
+                        double total, int slots) {
+    const double cells = double(n_tasks) * double(g.ncell);
+    // expected candidate tests per cell and task: the stencil's share of the
+    // grid, two thirds of whose points lie within reach of a cell
+    const double tests = total / cells * std::min(1.0, 0.67 * double(p.nfull) / double(g.ncell));
+    int64_t cpi = 1, slices = 1;
+    if (tune && tune->cells_per_item > 0) {
+        cpi = tune->cells_per_item;
+    } else if (!per_task) {
+        const double run = std::min(kRowTests / std::max(tests, 1.0), cells / (2.0 * slots));
+        // (the queue indexes items with 31 bits)
+        cpi = int64_t(std::min(double(g.n[0]), std::max({1.0, run, std::ceil(cells / double(1 << 30))})));
+        if (cpi == 1) slices = std::llround(std::max(1.0, std::min({8.0, 8.0 * slots / cells, tests / kSliceTests})));
+    }
+    p.cells_per_item = int(std::min<int64_t>(cpi, g.ncell));
+    p.nslice = int(slices);
+    p.items_per_task = int((g.ncell + p.cells_per_item - 1) / p.cells_per_item * slices);
 }
 
 static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task* tasks, int32_t n_tasks,
@@ -1176,15 +1236,6 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
                                       "coordinate range; build the mesh with smaller cells",
                         (long long)w, kmax);
     }
-    int cpi = tune && tune->cells_per_item > 0 ? tune->cells_per_item : 0;
-    if (cpi <= 0) {
-        // batched: one row of cells per item (neighbouring items share their j
-        // cells); one launch per task: single cells, to spread a task widest
-        cpi = (mode & LC_PER_TASK) ? 1 : std::max(1, g.n[0]);
-    }
-    cpi = int(std::min<int64_t>(cpi, g.ncell));
-    p.cells_per_item = cpi;
-    p.items_per_task = int((g.ncell + cpi - 1) / cpi);
     p.n_r = n_r;
     p.n_mu = n_mu;
     p.nbins = n_r * n_mu;
@@ -1312,7 +1363,7 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
             // bins or the midpoint kernel's j tables: two of them fit where
             // one 16-wave block did)
             int best = -1;
-            for (int w : {4, 8, 12, 16}) {
+            for (int w : {getenv("LC_W1") ? 1 : 4, getenv("LC_W1") ? 2 : 4, 4, 8, 12, 16}) {
                 if (w == 12 && !h16 && !mid) continue;
                 if (lds_of(sh, w) > ctx->max_lds_block) continue;
                 int o = 0;
@@ -1365,22 +1416,27 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
     // task order: largest first (cost ~ n_a * n_b, halved for auto pairs)
     std::vector<int32_t> order(n_tasks);
     std::vector<double> cost(n_tasks);
+    double total = 0;
     for (int t = 0; t < n_tasks; t++) {
         const int a = tasks[t].cat_a, bb = tasks[t].cat_b;
         const double na = double(cells->offsets[a + 1] - cells->offsets[a]);
         const double nb = double(cells->offsets[bb + 1] - cells->offsets[bb]);
         cost[t] = a == bb ? 0.5 * na * na : na * nb;
+        total += cost[t];
         order[t] = t;
     }
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
+    const bool per_task = (mode & LC_PER_TASK) != 0;
+    split_items(p, g, tune, per_task, n_tasks, total, pl.blocks);
     const int64_t n_items = int64_t(n_tasks) * p.items_per_task;
     if (n_items >= (int64_t(1) << 31))
         return fail(LC_ERR_OVERFLOW, "%lld work items exceed the 31-bit queue", (long long)n_items);
-    const bool per_task = (mode & LC_PER_TASK) != 0;
+    pl.blocks = int(std::min<int64_t>(pl.blocks, std::max<int64_t>(n_items, 1)));
     const int qorder = tune ? tune->queue_order : LC_QUEUE_XCD_RANGES;
     if (qorder != LC_QUEUE_XCD_RANGES && qorder != LC_QUEUE_XCD_DEALT && qorder != LC_QUEUE_SHARED)
         return fail(LC_ERR_INVALID, "queue_order = %d is not LC_QUEUE_XCD_RANGES, _DEALT or _SHARED", qorder);
     p.single_task = -1;
+    p.qstride = per_task ? 1 : kQStride;
     if (per_task) {
         // one queue holds the task's items; the other queues start empty
         p.qstart[0] = 0;
@@ -1390,19 +1446,24 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
         for (int t = 0; t < n_tasks; t++)
             pl.task_blocks[t] = int(std::max<int64_t>(1, std::min<int64_t>(p.items_per_task, pl.blocks)));
     } else if (qorder == LC_QUEUE_XCD_RANGES) {
-        // split the ordered tasks into kXcd contiguous ranges of equal cost;
-        // blocks of XCD x start on range x and move on when it is empty
-        double total = 0;
-        for (int t = 0; t < n_tasks; t++) total += cost[t];
+        // split the items into kXcd contiguous ranges of equal cost (a task's
+        // items count alike); blocks of XCD x start on range x and move on
+        // when it is empty
         p.qstart[0] = 0;
         double acc = 0;
         int x = 1;
-        for (int s = 0; s < n_tasks && x < kXcd; s++) {
-            acc += cost[order[s]];
-            while (x < kXcd && acc >= total * x / kXcd) p.qstart[x++] = uint32_t(int64_t(s + 1) * p.items_per_task);
+        for (int s = 0; s < n_tasks; s++) {
+            const double c = cost[order[s]];
+            while (x < kXcd && acc + c >= total * x / kXcd) {
+                const double part = c > 0 ? (total * x / kXcd - acc) / c : 1.0;
+                const int64_t in = std::llround(part * p.items_per_task);
+                p.qstart[x++] = uint32_t(int64_t(s) * p.items_per_task +
+                                         std::min<int64_t>(std::max<int64_t>(in, 0), p.items_per_task));
+            }
+            acc += c;
         }
         for (; x <= kXcd; x++) p.qstart[x] = uint32_t(n_items);
-        pl.n_queue = kXcd;
+        pl.n_queue = kXcd * kQStride;
     } else if (qorder == LC_QUEUE_XCD_DEALT) {
         // task s of the cost order goes to queue s mod kXcd: every queue
         // starts with large tasks and holds tasks of every size
@@ -1414,15 +1475,17 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
             p.qstart[x + 1] = uint32_t(int64_t(dealt.size()) * p.items_per_task);
         }
         order.swap(dealt);
-        pl.n_queue = kXcd;
+        pl.n_queue = kXcd * kQStride;
     } else {
         // one queue in cost order: blocks of the other XCDs find theirs empty
         // and move on to it
         p.qstart[0] = 0;
         for (int x = 1; x <= kXcd; x++) p.qstart[x] = uint32_t(n_items);
-        pl.n_queue = kXcd;
+        pl.n_queue = kXcd * kQStride;
     }
-    // staged block: tasks, order, stencil, squared edges, zeroed queue counters
+    // staged block: tasks, order, stencil, squared edges, zeroed queue
+    // counters (a line apart for the one persistent launch; a task's own
+    // launch has one busy queue)
     std::vector<int64_t> e2(n_r + 1);
     for (int k = 0; k <= n_r; k++) e2[k] = int64_t(b->r_edges[k]) * int64_t(b->r_edges[k]);
     std::vector<unsigned char> xtab(offsetof(ExactTab, e2) + sizeof(int64_t) * e2.size());
@@ -1441,6 +1504,7 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
         std::memcpy(xtab.data() + offsetof(ExactTab, e2), e2.data(), sizeof(int64_t) * e2.size());
     }
     std::vector<unsigned> qz(pl.n_queue, 0u);
+    pl.pad = per_task ? 0 : sizeof(unsigned) * size_t(kXcd * (kQStride - 1));
     auto put = [&](const void* src, size_t bytes) {
         size_t off = (pl.blob.size() + 255) & ~size_t(255);
         pl.blob.resize(off + bytes);
@@ -1595,7 +1659,8 @@ static lc_status check_count_args(const lc_cells* cells, const lc_task* tasks, i
 // ---------------------------------------------------------------------------
 // allocation-free variant: the staged plan lives in a static device array
 // ---------------------------------------------------------------------------
-constexpr size_t kScratchBytes = size_t(LC_NOALLOC_PLAN_BYTES);
+// (the spacing of the queue counters comes on top of the documented limit)
+constexpr size_t kScratchBytes = size_t(LC_NOALLOC_PLAN_BYTES) + sizeof(unsigned) * size_t(kXcd * kQStride);
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // Device address of `scratch` per device, taken once with that device
@@ -1677,10 +1742,10 @@ extern "C" lc_status lc_pair_count_batch_noalloc(const lc_cells* cells, const lc
     Plan pl;
     LC_TRY(make_plan(ctx, cells, tasks, n_tasks, b, mode, tune, pl));
     pl.blob.resize((pl.blob.size() + 3) & ~size_t(3), 0);
-    if (pl.blob.size() > kScratchBytes)
+    if (pl.blob.size() - pl.pad > size_t(LC_NOALLOC_PLAN_BYTES))
         return fail(LC_ERR_OVERFLOW, "the plan of %d tasks takes %zu bytes, more than the %zu bytes of the "
                                      "allocation-free call's static plan array; use lc_pair_count_batch",
-                    n_tasks, pl.blob.size(), kScratchBytes);
+                    n_tasks, pl.blob.size() - pl.pad, size_t(LC_NOALLOC_PLAN_BYTES));
     unsigned char* dev = nullptr;
     LC_TRY(scratch_ptr(ctx->device, &dev));
     hipStream_t s = (hipStream_t)stream;
