@@ -360,9 +360,16 @@ static int grid_for(int64_t n, int threads, int n_cu) {
 using namespace lc;
 
 static void free_cells_mem(lc_cells* c) {
-    if (!c) return;
-    if (c->pts) (void)hipFree(c->pts);
-    if (c->cs) (void)hipFree(c->cs);
+    if (!c || (!c->pts && !c->cs)) return;
+    // any stream may have counted on the mesh: as hipFree would, wait for all
+    // of them before the buffers can be handed out again
+    int cur = c->device;
+    (void)hipGetDevice(&cur);
+    if (cur != c->device) (void)hipSetDevice(c->device);
+    (void)hipDeviceSynchronize();
+    dev_free_idle(c->pts);
+    dev_free_idle(c->cs);
+    if (cur != c->device) (void)hipSetDevice(cur);
     c->pts = nullptr;
     c->cs = nullptr;
 }
@@ -499,8 +506,7 @@ extern "C" lc_status lc_build_cells(const int32_t* xyz, int64_t n_total, const i
     // 4 extra points of padding: pair counting reads whole groups of four
     size_t pts_bytes = size_t(std::max<int64_t>(n_total, 1) + 4) * 3 * sizeof(float);
     size_t cs_bytes = size_t(ntot_cells + 1) * sizeof(int64_t);
-    if (hipMalloc(&cells->pts, pts_bytes) != hipSuccess || hipMalloc(&cells->cs, cs_bytes) != hipSuccess) {
-        (void)hipGetLastError();
+    if (dev_alloc((void**)&cells->pts, pts_bytes, s) != LC_OK || dev_alloc((void**)&cells->cs, cs_bytes, s) != LC_OK) {
         free_cells_mem(cells);
         delete cells;
         return fail(LC_ERR_NOMEM, "mesh allocation (%zu + %zu bytes) failed", pts_bytes, cs_bytes);

@@ -6,7 +6,10 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <list>
+#include <map>
 #include <mutex>
+#include <unordered_map>
 #include <string>
 #include <vector>
 
@@ -44,17 +47,38 @@ lc_status fail(lc_status code, const char* fmt, ...);
 // ---------------------------------------------------------------------------
 // per-device context
 // ---------------------------------------------------------------------------
+// One pinned block of a small ring for host->device parameter copies; its
+// event tells when the copy out of it is done.
+struct PinnedSlot {
+    void* p = nullptr;
+    size_t size = 0;
+    hipEvent_t ev = nullptr;
+    bool pending = false;
+};
+constexpr int kPinnedSlots = 8;
+
+// A device buffer of the scratch cache: on stream s up to event ev (recorded
+// when it was freed; `idle`: no work uses it, ev says nothing).
+struct ScratchBlock {
+    void* p = nullptr;
+    size_t size = 0;
+    hipEvent_t ev = nullptr;
+    hipStream_t s = nullptr;
+    bool idle = true;
+};
+
 struct DeviceCtx {
     int device = -1;
     int n_cu = 0;
     size_t max_lds_block = 65536;
-    std::mutex mu;
-    // pinned staging for small host->device parameter copies; guarded by an
-    // event so the host never overwrites bytes a pending copy still reads
-    void* pinned = nullptr;
-    size_t pinned_size = 0;
-    hipEvent_t pinned_ev = nullptr;
-    bool pinned_pending = false;
+    std::mutex mu;                      // guards the pinned ring
+    PinnedSlot pinned[kPinnedSlots];
+    int pinned_next = 0;
+    std::mutex scratch_mu;              // guards the scratch cache
+    std::list<ScratchBlock> scratch;    // freed buffers, oldest first
+    size_t scratch_bytes = 0;           // their sum
+    size_t scratch_cap = 0;             // and its bound
+    std::unordered_map<void*, ScratchBlock> scratch_live;
 };
 
 // Context of the current device (created on first use).
@@ -75,10 +99,12 @@ class Stager {
     std::vector<unsigned char> host_;
 };
 
-// Stream-ordered device allocation (hipMallocAsync / hipFreeAsync on the
-// device's default pool, whose release threshold is raised at set-up).
+// Stream-ordered device memory from the device's scratch cache: dev_free
+// hands the buffer back as of this point of stream s, dev_alloc takes one
+// that is ready for stream s.  dev_free_idle: no queued work uses the buffer.
 lc_status dev_alloc(void** p, size_t bytes, hipStream_t s);
 void dev_free(void* p, hipStream_t s);
+void dev_free_idle(void* p);
 
 // A stream-ordered device buffer that is freed on its stream when it goes
 // out of scope (or at reset()), so every early return releases what was
