@@ -41,3 +41,53 @@ def test_small_batches_bit_exact(name, points, r_max, n_mock, pool, los):
         ref = oracle.count_pairs(cats.cat(a), None if a == b else cats.cat(b), wl.r_edges_units, wl.n_mu,
                                  wl.box_units, los, pi_max=wl.pi_max_units)
         assert np.array_equal(got[t], ref), (t, a, b)
+
+
+# rows per block: 256 bins hold many rows, a last group narrower than the
+# others, one row, and less than one row (n_mu past 256)
+@pytest.mark.parametrize("n_r,n_mu", [(1, 1), (300, 1), (7, 100), (40, 50), (5, 129), (3, 256), (3, 257), (2, 1024)])
+@pytest.mark.parametrize("n_sub", [1, 2, 7])
+def test_xi_row_groups(n_r, n_mu, n_sub):
+    import torch
+
+    from paper_2205_11852_amd import lc
+
+    n_mock, sizes = 3, np.array([900, 1001, 77, 500, 600, 700, 800, 901, 650, 420][:3 + n_sub], dtype=np.int64)
+    rng = np.random.default_rng(n_r * 1000 + n_mu)
+    tasks = [(s, s) for s in range(3, 3 + n_sub)]
+    est = []
+    for m in range(n_mock):
+        est.append([len(tasks)] + [len(tasks) + 1 + i for i in range(n_sub)] + list(range(n_sub)))
+        tasks += [(m, m)] + [(m, s) for s in range(3, 3 + n_sub)]
+    # a few empty bins: those estimates are NaN
+    counts = rng.integers(0, 4, (len(tasks), n_r, n_mu)) * rng.integers(0, 100000, (len(tasks), n_r, n_mu))
+    P = n_r * n_mu + 3 * n_r
+    dev = torch.as_tensor(counts, device="cuda")
+    xi = torch.empty((n_mock, P), dtype=torch.float64, device="cuda")
+    lc.lc_xi_split(dev, tasks, sizes, est, n_sub, n_r, n_mu, xi)
+    W = oracle.legendre_weights(n_mu)
+
+    def check(got, dd, drs, rrs, nd, nrs):
+        d = dd / (nd * (nd - 1) / 2.0)
+        dr = sum(c / (nd * n) for c, n in zip(drs, nrs)) / len(nrs)
+        rr = sum(c / (n * (n - 1) / 2.0) for c, n in zip(rrs, nrs)) / len(nrs)
+        with np.errstate(divide="ignore", invalid="ignore"):
+            ref = np.where(rr == 0, np.nan, (d - 2.0 * dr) / rr + 1.0)
+            scale = np.where(rr == 0, np.nan, (d + 2.0 * dr) / rr + 1.0)
+        full = np.concatenate([ref.ravel()] + [(ref * w).sum(1) for w in W])
+        size = np.concatenate([scale.ravel()] + [(scale * abs(w)).sum(1) for w in W])
+        assert np.array_equal(np.isnan(got), np.isnan(full))
+        ok = ~np.isnan(full)
+        assert np.all(abs(got - full)[ok] <= 1e-12 * size[ok])
+
+    got = xi.cpu().numpy()
+    for m, e in enumerate(est):
+        check(got[m], counts[e[0]], counts[e[1:1 + n_sub]], counts[e[1 + n_sub:]], sizes[m], sizes[3:].astype(float))
+    if n_sub == 2:
+        three = torch.empty((n_mock, 3, P), dtype=torch.float64, device="cuda")
+        lc.lc_xi_multipoles(dev, tasks, sizes, est, n_r, n_mu, three)
+        t = three.cpu().numpy()
+        assert np.array_equal(t[:, 2], got, equal_nan=True)
+        for m, e in enumerate(est):
+            for q in range(2):
+                check(t[m, q], counts[e[0]], [counts[e[1 + q]]], [counts[e[3 + q]]], sizes[m], [float(sizes[3 + q])])
