@@ -602,6 +602,299 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 8 : 4))) void k_hh_column(double
     }
 }
 
+// ---------------------------------------------------------------------------
+// Householder tridiagonalisation in one launch, for up to kTrRows kTrMaxBlocks
+// rows.  A launch per column (above) is bound by the launch itself and by
+// reading and writing the trailing matrix; here the matrix never leaves the
+// registers.  Block b holds rows b, b + B, b + 2 B, ... (kTrRows of them, so
+// every block keeps work until the end), thread t columns t + 512 u of each
+// of them, and with them elements t + 512 u of v, w and the current row: the
+// rank-2 update and the product A22 v need no other thread's data but the
+// rows' own v and w.  At the end of a column a block publishes, for each of
+// its rows r, p_r and the element A[r][k+1] of the next row to reflect (A is
+// symmetric), and every block forms the same v, K and w from them.  What
+// bounds a column is this exchange between all blocks, there and back, and
+// three barriers in each: 3.0 us a column with 15 blocks, 3.6 us with 68 and
+// 5.0 us with 250, where the reads of the exchange add up (2000 rows: 24.4 ms
+// in a launch per column, 10.0 ms here; 540 rows: 3.5 and 1.9 ms; 120 rows:
+// 0.65 and 0.36 ms).
+//
+// The exchange: slots hold kTrEmpty until a value is there, so a value is its
+// own flag and a reader polls the values themselves (agent-scope relaxed
+// accesses, which go to the point where the XCDs meet).  Three buffers take
+// turns: a block publishes step k only after it has read all of step k-1, so
+// once a block has read all of step k-1, everyone is done with step k-2, and
+// the block empties its own slots of that buffer, which takes step k+1; its
+// stores have completed before its next publication.
+//
+// Blocks that are not all resident at once (other work holds the CUs) would
+// wait for each other; every wait is bounded by `spin` polls, after which the
+// block raises *gave_up and ends, the others follow, and the caller goes
+// through the columns launch by launch.
+// ---------------------------------------------------------------------------
+constexpr int kTrThreads = 512;
+constexpr int kTrRows = 8;
+constexpr int kTrMaxBlocks = 256;
+constexpr int kTrSpin = 40000;   // some tens of milliseconds
+constexpr unsigned long long kTrEmpty = 0x7FF4DEAD5EED0001ull;  // a NaN no operation returns
+
+// x plus the lane's neighbour under a DPP control (0 where there is none)
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double dpp_add(double x) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    const int l2 = __builtin_amdgcn_update_dpp(0, lo, CTRL, ROWS, 0xF, true);
+    const int h2 = __builtin_amdgcn_update_dpp(0, hi, CTRL, ROWS, 0xF, true);
+    return x + __hiloint2double(h2, l2);
+}
+
+// Sum over the wave (valid in lane 63).
+__device__ __forceinline__ double wave_sum63(double x) {
+    x = dpp_add<0x111>(x);        // row_shr:1
+    x = dpp_add<0x112>(x);        // row_shr:2
+    x = dpp_add<0x114>(x);        // row_shr:4
+    x = dpp_add<0x118>(x);        // row_shr:8
+    x = dpp_add<0x142, 0xA>(x);   // row_bcast:15 into rows 1 and 3
+    x = dpp_add<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+
+// Sum over the lane's group of eight.
+__device__ __forceinline__ double octet_sum(double x) {
+    x = dpp_add<0xB1>(x);    // quad_perm [1, 0, 3, 2]
+    x = dpp_add<0x4E>(x);    // quad_perm [2, 3, 0, 1]
+    return dpp_add<0x141>(x);  // row_half_mirror
+}
+
+// a + b with the upper half (H 32) or odd rows of 16 (H 16) of a exchanged
+// for the lower half or even rows of b: sums of a in the lanes that kept it,
+// of b in the others.
+template <int H>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    const unsigned al = __double2loint(a), ah = __double2hiint(a), bl = __double2loint(b), bh = __double2hiint(b);
+    u2 l, h;
+    if (H == 32) {
+        l = __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+        h = __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    } else {
+        l = __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+        h = __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
+    }
+    return __hiloint2double(int(h[0]), int(l[0])) + __hiloint2double(int(h[1]), int(l[1]));
+}
+
+// Wave sums of eight values: lane l returns the sum of acc[l >> 3].
+__device__ __forceinline__ double wave_sum8(const double (&acc)[kTrRows], int lane) {
+    double u[4], t[2];
+#pragma unroll
+    for (int i = 0; i < 4; i++) u[i] = swap_add<32>(acc[i], acc[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; i++) t[i] = swap_add<16>(u[i], u[i + 2]);
+    const bool up = (lane & 8) != 0;
+    const double y = up ? t[1] : t[0], z = up ? t[0] : t[1];
+    const int zl = __builtin_amdgcn_update_dpp(0, __double2loint(z), 0x128, 0xF, 0xF, true);  // row_ror:8
+    const int zh = __builtin_amdgcn_update_dpp(0, __double2hiint(z), 0x128, 0xF, 0xF, true);
+    return octet_sum(y + __hiloint2double(zh, zl));
+}
+
+__device__ __forceinline__ void tr_put(unsigned long long* q, unsigned long long v) {
+    __hip_atomic_store(q, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long tr_get(const unsigned long long* q) {
+    return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ void k_tr_empty(unsigned long long* __restrict__ q, int64_t n, int* __restrict__ gave_up) {
+    for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
+        q[i] = kTrEmpty;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *gave_up = 0;
+}
+
+// E columns per thread (n <= 512 E).  C: the block at (off, off) of a matrix
+// of row length P.  q: [3][2][n] slots (p, then the next row's elements).
+// Element i of a thread's column c < k (reflected already) is kept zero.
+template <int E>
+__global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restrict__ C, int64_t P, int64_t off, int n,
+                                                           const CheckFlags* fl, unsigned long long* __restrict__ q,
+                                                           int spin, int* __restrict__ gave_up,
+                                                           double* __restrict__ d, double* __restrict__ e) {
+    constexpr int R = kTrRows, NW = kTrThreads / 64;
+    __shared__ double red[2][NW];     // wave sums of v.p and |x|^2
+    __shared__ double sums[NW][R];    // wave sums of the rows' products
+    __shared__ double rv[R], rw[R];   // v and w at the block's rows
+    __shared__ double rnext[R];       // A[r][k+1] at the block's rows
+    __shared__ double at_k[3], at_k1; // v, p and A[k][k] at k; x at k + 1
+    __shared__ int failed;
+    if (fl->nan_seen) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x, B = gridDim.x;
+    const int rlast = b + (n - 1 - b) / B * B;  // the block's last row
+    double a[R][E], v[E];
+    int own[E];  // this thread's columns that are rows of this block: which one, or -1
+#pragma unroll
+    for (int u = 0; u < E; u++) {
+        const int c = tid + u * kTrThreads;
+        own[u] = (c < n && c % B == b) ? c / B : -1;
+        v[u] = 0.0;
+#pragma unroll
+        for (int i = 0; i < R; i++) {
+            const int r = b + i * B;
+            a[i][u] = (r < n && c < n) ? C[(off + r) * P + off + c] : 0.0;
+        }
+    }
+    // the first row to reflect, with no update pending
+    const int myrow = b + tid * B;  // (tid < R) the row whose slots this thread fills first
+    unsigned long long* const q0 = q;
+    const int64_t step_words = 2 * int64_t(n);
+    if (tid < R && myrow < n) {
+        tr_put(q0 + 2 * step_words + myrow, 0ull);
+        tr_put(q0 + 2 * step_words + n + myrow,
+               (unsigned long long)__double_as_longlong(C[(off + myrow) * P + off]));
+    }
+    if (tid == 0) failed = 0;
+    double tau = 0.0;
+    int buf = 2;  // buffer of step k - 1
+    __syncthreads();
+    for (int k = 0; k + 1 < n; k++) {
+        if (rlast <= k) return;  // none of the block's rows is left (row n - 1's block stays)
+        const int buf_next = buf == 2 ? 0 : buf + 1;          // step k's
+        const int buf_old = buf_next == 2 ? 0 : buf_next + 1;  // step k - 2's, which step k + 1 takes
+        unsigned long long* const qp = q0 + buf * step_words;
+        double w[E], x[E];
+        {
+            unsigned long long sp[E], sa[E];
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < E; u++) {
+                const int c = tid + u * kTrThreads;
+                sp[u] = sa[u] = 0ull;
+                if (c >= k && c < n) {
+                    sp[u] = tr_get(qp + c);
+                    sa[u] = tr_get(qp + n + c);
+                }
+            }
+            for (int polls = 0;; polls++) {
+                ok = true;
+#pragma unroll
+                for (int u = 0; u < E; u++) ok = ok && sp[u] != kTrEmpty && sa[u] != kTrEmpty;
+                if (ok || polls >= spin) break;
+#pragma unroll
+                for (int u = 0; u < E; u++) {
+                    const int c = tid + u * kTrThreads;
+                    if (sp[u] == kTrEmpty) sp[u] = tr_get(qp + c);
+                    if (sa[u] == kTrEmpty) sa[u] = tr_get(qp + n + c);
+                }
+            }
+            if (!ok) failed = 1;
+#pragma unroll
+            for (int u = 0; u < E; u++) {
+                w[u] = __longlong_as_double((long long)sp[u]);  // p for now
+                x[u] = __longlong_as_double((long long)sa[u]);  // the row before the pending update
+            }
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < E; u++) {
+            s += v[u] * w[u];
+            if (tid + u * kTrThreads == k) {
+                at_k[0] = v[u];
+                at_k[1] = w[u];
+                at_k[2] = x[u];
+            }
+        }
+        s = wave_sum63(s);
+        if (lane == 63) red[0][wv] = s;
+        __syncthreads();
+        if (failed) {
+            if (tid == 0) __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        if (tid < R && myrow < n) {
+            tr_put(q0 + buf_old * step_words + myrow, kTrEmpty);
+            tr_put(q0 + buf_old * step_words + n + myrow, kTrEmpty);
+        }
+        // the pending update's K and w, and row k brought up to date
+        double K = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; i++) K += red[0][i];
+        K *= 0.5 * tau;
+        const double vk = at_k[0], wk = at_k[1] - K * vk;
+        s = 0.0;
+#pragma unroll
+        for (int u = 0; u < E; u++) {
+            const int c = tid + u * kTrThreads;
+            w[u] -= K * v[u];
+            x[u] = c > k && c < n ? x[u] - (vk * w[u] + wk * v[u]) : 0.0;
+            s += x[u] * x[u];
+            if (c == k + 1) at_k1 = x[u];
+            if (own[u] >= 0) {
+                rv[own[u]] = v[u];
+                rw[own[u]] = w[u];
+            }
+        }
+        s = wave_sum63(s);
+        if (lane == 63) red[1][wv] = s;
+        __syncthreads();
+        double norm2 = 0.0;
+#pragma unroll
+        for (int i = 0; i < NW; i++) norm2 += red[1][i];
+        const double x0 = at_k1;
+        const double nrm = sqrt(norm2);
+        const double alpha = x0 > 0 ? -nrm : nrm;  // reflect x onto alpha e1
+        const double v0 = x0 - alpha;
+        const double vnorm2 = norm2 - x0 * x0 + v0 * v0;
+        const bool trivial = !(vnorm2 > 0.0) || (norm2 - x0 * x0) <= 0.0;
+        tau = trivial ? 0.0 : 2.0 / vnorm2;
+        if (rlast == n - 1 && tid == 0) {
+            d[k] = at_k[2] - 2.0 * vk * wk;
+            e[k] = trivial ? x0 : alpha;
+        }
+        double acc[R];
+#pragma unroll
+        for (int i = 0; i < R; i++) acc[i] = 0.0;
+#pragma unroll
+        for (int u = 0; u < E; u++) {
+            const int c = tid + u * kTrThreads;
+            const double vn = trivial ? 0.0 : (c == k + 1 ? v0 : x[u]);
+#pragma unroll
+            for (int i = 0; i < R; i++) {
+                a[i][u] -= rv[i] * w[u] + rw[i] * v[u];
+                acc[i] += a[i][u] * vn;
+            }
+            if (c == k + 1) {
+#pragma unroll
+                for (int i = 0; i < R; i++) rnext[i] = a[i][u];
+            }
+            v[u] = vn;
+        }
+        s = wave_sum8(acc, lane);
+        if ((lane & 7) == 0) sums[wv][lane >> 3] = s;
+        __syncthreads();
+        if (wv == 0) {
+            const int i = lane >> 3, r = b + i * B;
+            const double p = octet_sum(sums[lane & 7][i]);
+            // the emptied slots before the new values
+            __builtin_amdgcn_s_waitcnt(0);
+            if ((lane & 7) == 0 && r > k && r < n) {
+                unsigned long long* const qn = q0 + buf_next * step_words;
+                tr_put(qn + r, (unsigned long long)__double_as_longlong(trivial ? 0.0 : tau * p));
+                tr_put(qn + n + r, (unsigned long long)__double_as_longlong(rnext[i]));
+            }
+        }
+        buf = buf_next;
+    }
+    if (rlast == n - 1) {
+#pragma unroll
+        for (int u = 0; u < E; u++)
+            if (tid + u * kTrThreads == n - 1) {
+                const int il = (n - 1) / B;
+#pragma unroll
+                for (int i = 0; i < R; i++)
+                    if (i == il) d[n - 1] = a[i][u];
+            }
+    }
+}
+
 // The last 2 x 2 block (rows n-2, n-1 = indices 0, 1 of the pending update's
 // A22) gives the last diagonal and off-diagonal entries.  One block.
 __global__ void k_hh_tail(const double* __restrict__ W, int64_t n, HhPending q, double* __restrict__ d,
@@ -712,6 +1005,26 @@ static int nblocks(int64_t n, int threads, int cap = 4096) {
     return int(std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, cap)));
 }
 
+// Tridiagonalisation with one launch per column, on a fresh copy W of the
+// block.
+static void tridiag_columns(const double* C, int64_t P, int64_t off, int64_t n, double* W, CheckFlags* fl,
+                            double* const (&v)[2], double* const (&pv)[2], double* const (&vpp)[2], double* tau,
+                            double* d, double* e, hipStream_t s) {
+    k_copy_block<<<nblocks(n * n, 256), 256, 0, s>>>(C, P, off, n, W, fl);
+    HhPending q{nullptr, nullptr, nullptr, nullptr, 0};
+    for (int64_t k = 0; k + 2 < n; k++) {
+        const int64_t m = n - k - 1;
+        const int64_t n1 = (m + kHhRows - 1) / kHhRows;
+        const int c = int(k & 1);
+        if (m >= 256)
+            k_hh_column<4><<<unsigned(n1), 64 * kHhRows * 4, 0, s>>>(W, n, k, q, v[c], tau + c, d, e, pv[c], vpp[c]);
+        else
+            k_hh_column<1><<<unsigned(n1), 64 * kHhRows, 0, s>>>(W, n, k, q, v[c], tau + c, d, e, pv[c], vpp[c]);
+        q = HhPending{v[c], pv[c], tau + c, vpp[c], n1};
+    }
+    k_hh_tail<<<1, 256, 0, s>>>(W, n, q, d, e);
+}
+
 // Check one diagonal block [off, off+n) of C.  Writes chol_ok, n_neg, min, max.
 static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n, hipStream_t s,
                              int32_t* chol_ok, int32_t* n_neg, double* mn, double* mx) {
@@ -726,11 +1039,11 @@ static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n,
     LC_TRY(Wb.alloc(size_t(n * n), s));
     const int64_t naux = 8 * n + 32;
     LC_TRY(auxb.alloc(size_t(naux), s));
-    LC_TRY(flb.alloc(2, s));
+    LC_TRY(flb.alloc(1, s));
     double* W = Wb.get();
     double* aux = auxb.get();
     CheckFlags* fl = flb.get();
-    k_zero_flags<<<1, 64, 0, s>>>(fl, 2);
+    k_zero_flags<<<1, 64, 0, s>>>(fl, 1);
     // two sets of Householder buffers: the launch for column k reads step
     // k-1's set while it fills its own
     double* const v[2] = {aux, aux + n};
@@ -752,27 +1065,37 @@ static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n,
             k_potrf_update<<<int(T * (T + 1) / 2), 256, 0, s>>>(W, n, k0, nb, fl);
         }
     }
-    // eigenvalues: fresh copy, tridiagonalise, bisect
-    k_copy_block<<<nblocks(n * n, 256), 256, 0, s>>>(C, P, off, n, W, fl + 1);
-    HhPending q{nullptr, nullptr, nullptr, nullptr, 0};
-    for (int64_t k = 0; k + 2 < n; k++) {
-        const int64_t m = n - k - 1;
-        const int64_t n1 = (m + kHhRows - 1) / kHhRows;
-        const int c = int(k & 1);
-        if (m >= 256)
-            k_hh_column<4><<<unsigned(n1), 64 * kHhRows * 4, 0, s>>>(W, n, k, q, v[c], tau + c, d, e, pv[c], vpp[c]);
-        else
-            k_hh_column<1><<<unsigned(n1), 64 * kHhRows, 0, s>>>(W, n, k, q, v[c], tau + c, d, e, pv[c], vpp[c]);
-        q = HhPending{v[c], pv[c], tau + c, vpp[c], n1};
+    // eigenvalues: tridiagonalise, bisect
+    DevBuf<unsigned long long> slots;
+    DeviceCtx* ctx;
+    LC_TRY(get_ctx(&ctx));
+    const bool resident = n <= int64_t(kTrRows) * std::min(kTrMaxBlocks, ctx->n_cu) && n <= 4 * kTrThreads;
+    if (resident) {
+        LC_TRY(slots.alloc(size_t(6 * n) + 1, s));
+        int* const gave_up = reinterpret_cast<int*>(slots.get() + 6 * n);
+        k_tr_empty<<<nblocks(6 * n, 256), 256, 0, s>>>(slots.get(), 6 * n, gave_up);
+        const unsigned B = unsigned((n + kTrRows - 1) / kTrRows);
+        auto* kern = n <= kTrThreads ? k_tridiag<1> : n <= 2 * kTrThreads ? k_tridiag<2> : k_tridiag<4>;
+        kern<<<B, kTrThreads, 0, s>>>(C, P, off, int(n), fl, slots.get(), kTrSpin, gave_up, d, e);
+    } else {
+        tridiag_columns(C, P, off, n, W, fl, v, pv, vpp, tau, d, e, s);
     }
-    k_hh_tail<<<1, 256, 0, s>>>(W, n, q, d, e);
-    k_bisect<<<3, kBisectThreads, 0, s>>>(d, e, n, fl + 1, res);
-    CheckFlags hf[2];
+    k_bisect<<<3, kBisectThreads, 0, s>>>(d, e, n, fl, res);
+    CheckFlags hf;
     double hr[3];
-    LC_TRY_HIP(hipMemcpyAsync(hf, fl, sizeof hf, hipMemcpyDeviceToHost, s));
+    int hg = 0;
+    if (resident) LC_TRY_HIP(hipMemcpyAsync(&hg, slots.get() + 6 * n, sizeof hg, hipMemcpyDeviceToHost, s));
+    LC_TRY_HIP(hipMemcpyAsync(&hf, fl, sizeof hf, hipMemcpyDeviceToHost, s));
     LC_TRY_HIP(hipMemcpyAsync(hr, res, sizeof hr, hipMemcpyDeviceToHost, s));
     LC_TRY_HIP(hipStreamSynchronize(s));
-    *chol_ok = (!hf[0].nan_seen && !hf[0].chol_fail) ? 1 : 0;
+    if (hg) {
+        // the blocks were not all resident: column by column instead
+        tridiag_columns(C, P, off, n, W, fl, v, pv, vpp, tau, d, e, s);
+        k_bisect<<<3, kBisectThreads, 0, s>>>(d, e, n, fl, res);
+        LC_TRY_HIP(hipMemcpyAsync(hr, res, sizeof hr, hipMemcpyDeviceToHost, s));
+        LC_TRY_HIP(hipStreamSynchronize(s));
+    }
+    *chol_ok = (!hf.nan_seen && !hf.chol_fail) ? 1 : 0;
     *n_neg = int32_t(hr[2]);
     *mn = hr[0];
     *mx = hr[1];
