@@ -25,6 +25,10 @@ namespace lc {
 // ---------------------------------------------------------------------------
 // mean and deviations
 // ---------------------------------------------------------------------------
+static int nblocks(int64_t n, int threads, int cap = 4096) {
+    return int(std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, cap)));
+}
+
 constexpr int kMeanRows = 64;
 
 // partial[c][j] = sum of xi[n][j] over rows n of chunk c (j < 3P)
@@ -48,20 +52,6 @@ __global__ void k_mean_final(const double* __restrict__ partial, int64_t nchunk,
     mean[j] = s / double(n_mock);
 }
 
-// dev64[e][n][p] = xi[n][e][p] - mean[e][p]    (ne estimates per mock; ld = P)
-__global__ void k_dev64(const double* __restrict__ xi, const double* __restrict__ mean, int64_t n_mock,
-                        int64_t P, int64_t ne, double* __restrict__ dev) {
-    const int64_t tot = ne * n_mock * P;
-    for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < tot;
-         t += int64_t(gridDim.x) * blockDim.x) {
-        const int64_t p = t % P;
-        const int64_t r = t / P;
-        const int64_t n = r % n_mock;
-        const int64_t e = r / n_mock;
-        dev[t] = xi[n * ne * P + e * P + p] - mean[e * P + p];
-    }
-}
-
 // dev32[e][n][p] (ld = Ppad, Npad rows, zero padded) = float(xi - mean)
 __global__ void k_dev32(const double* __restrict__ xi, const double* __restrict__ mean, int64_t n_mock,
                         int64_t P, int64_t ne, int64_t Npad, int64_t Ppad, float* __restrict__ dev) {
@@ -79,7 +69,17 @@ __global__ void k_dev32(const double* __restrict__ xi, const double* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// SYRK, float64: 64x64 tiles, 16x16 threads with 4x4 outputs each
+// SYRK, float64: C = D^T D / (N - 1) over lower-triangle tiles of 64 x 64,
+// four waves of 32 x 32, each 2 x 2 blocks of v_mfma_f64_16x16x4 (operand
+// layout: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j =
+// l % 16]; register r of lane l holds D[i = l / 16 + 4 r][j = l % 16]).  The
+// deviations are formed while a slab of 16 mocks is staged, and the next
+// slab's loads are in flight over the products.  What bounds short vectors is
+// blocks: 540 elements give 45 tiles, so the mocks are split over gridDim.z
+// as well and the parts summed in order (k_syrk_sum).  3000 mocks of 540 x 3:
+// 0.80 ms from float64 VALU products of a stored copy of the deviations,
+// 0.175 ms here; error against extended precision 1.5e-15 then, 1.6e-16 in
+// eight parts.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void tri_tile(int t, int& ti, int& tj) {
     // t enumerates (ti, tj) with tj <= ti
@@ -89,51 +89,98 @@ __device__ __forceinline__ void tri_tile(int t, int& ti, int& tj) {
     tj = t - ti * (ti + 1) / 2;
 }
 
-__global__ __launch_bounds__(256) void k_syrk64(const double* __restrict__ dev, int64_t n_mock, int64_t P,
-                                                double denom, double* __restrict__ cov) {
-    __shared__ double As[16][64 + 1];
-    __shared__ double Bs[16][64 + 1];
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kST = 64;          // tile
+constexpr int kSK = 16;          // mocks per slab
+constexpr int kSLd = kST + 16;   // row stride in LDS: the two rows a half wave reads lie in different banks
+
+// Element (i, j) of tile (ti, tj) held in register q of thread t.
+__device__ __forceinline__ void syrk64_at(int q, int t, int& i, int& j) {
+    const int lane = t & 63, wid = t >> 6, u = q >> 3, v = (q >> 2) & 1, r = q & 3;
+    i = (wid >> 1) * 32 + 16 * u + (lane >> 4) + 4 * r;
+    j = (wid & 1) * 32 + 16 * v + (lane & 15);
+}
+
+// x: element p of estimate e of mock n at x[n ld + e P + p].  split: mocks per
+// gridDim.z part (a multiple of kSK); part != NULL: raw sums go there.
+__global__ __launch_bounds__(256) void k_syrk64(const double* __restrict__ x, int64_t ld,
+                                                const double* __restrict__ mean, int64_t n_mock, int64_t P,
+                                                int64_t split, double denom, double* __restrict__ part,
+                                                double* __restrict__ cov) {
+    __shared__ double As[2][kSK][kSLd];
+    __shared__ double Bs[2][kSK][kSLd];
     const int e = blockIdx.y;
     int ti, tj;
     tri_tile(blockIdx.x, ti, tj);
-    const int64_t i0 = int64_t(ti) * 64, j0 = int64_t(tj) * 64;
-    const double* D = dev + int64_t(e) * n_mock * P;
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    double acc[4][4] = {};
-    for (int64_t n0 = 0; n0 < n_mock; n0 += 16) {
-        for (int q = threadIdx.x; q < 16 * 64; q += 256) {
-            const int kk = q >> 6, c = q & 63;
-            const int64_t n = n0 + kk;
-            As[kk][c] = (n < n_mock && i0 + c < P) ? D[n * P + i0 + c] : 0.0;
-            Bs[kk][c] = (n < n_mock && j0 + c < P) ? D[n * P + j0 + c] : 0.0;
+    const int64_t i0 = int64_t(ti) * kST, j0 = int64_t(tj) * kST;
+    const int64_t nb = int64_t(blockIdx.z) * split, ne = min(nb + split, n_mock);
+    // this thread stages column c of the tile, mocks k4, k4 + 4, ... of a slab
+    const int c = threadIdx.x & 63, k4 = threadIdx.x >> 6;
+    const bool ai = i0 + c < P, bj = j0 + c < P;
+    const double* xa = x + e * P + (ai ? i0 + c : 0);
+    const double* xb = x + e * P + (bj ? j0 + c : 0);
+    const double ma = ai ? mean[e * P + i0 + c] : 0.0, mb = bj ? mean[e * P + j0 + c] : 0.0;
+    double pa[kSK / 4], pb[kSK / 4];
+    auto load = [&](int64_t n0) {
+#pragma unroll
+        for (int q = 0; q < kSK / 4; q++) {
+            const int64_t n = n0 + k4 + 4 * q;
+            pa[q] = ai && n < ne ? xa[n * ld] - ma : 0.0;
+            pb[q] = bj && n < ne ? xb[n * ld] - mb : 0.0;
         }
-        __syncthreads();
+    };
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int wr = (wid >> 1) * 32, wc = (wid & 1) * 32, lc = lane & 15, lk = lane >> 4;
+    f64x4 acc[2][2] = {};
+    load(nb);
+    int buf = 0;
+    for (int64_t n0 = nb; n0 < ne; n0 += kSK, buf ^= 1) {
 #pragma unroll
-        for (int kk = 0; kk < 16; kk++) {
-            double a[4], b[4];
+        for (int q = 0; q < kSK / 4; q++) {
+            As[buf][k4 + 4 * q][c] = pa[q];
+            Bs[buf][k4 + 4 * q][c] = pb[q];
+        }
+        __syncthreads();  // (the other buffer was read before the last barrier)
+        load(n0 + kSK);
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                a[r] = As[kk][ty * 4 + r];
-                b[r] = Bs[kk][tx * 4 + r];
+        for (int k = 0; k < kSK; k += 4) {
+            double a[2], b[2];
+#pragma unroll
+            for (int u = 0; u < 2; u++) {
+                a[u] = As[buf][k + lk][wr + 16 * u + lc];
+                b[u] = Bs[buf][k + lk][wc + 16 * u + lc];
             }
 #pragma unroll
-            for (int r = 0; r < 4; r++)
+            for (int u = 0; u < 2; u++)
 #pragma unroll
-                for (int c = 0; c < 4; c++) acc[r][c] = fma(a[r], b[c], acc[r][c]);
+                for (int v = 0; v < 2; v++)
+                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[v], acc[u][v], 0, 0, 0);
         }
-        __syncthreads();
     }
+    const int64_t tile = (int64_t(blockIdx.z) * gridDim.y + e) * gridDim.x + blockIdx.x;
     double* C = cov + int64_t(e) * P * P;
-    for (int r = 0; r < 4; r++)
-        for (int c = 0; c < 4; c++) {
-            const int64_t i = i0 + ty * 4 + r, j = j0 + tx * 4 + c;
-            if (i < P && j < P) {
-                const double v = acc[r][c] / denom;
-                C[i * P + j] = v;
-                if (ti != tj) C[j * P + i] = v;
-            }
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const double s = acc[q >> 3][(q >> 2) & 1][q & 3];
+        if (part) {
+            part[(tile * 16 + q) * 256 + threadIdx.x] = s;
+            continue;
         }
+        int il, jl;
+        syrk64_at(q, threadIdx.x, il, jl);
+        const int64_t i = i0 + il, j = j0 + jl;
+        if (i < P && j < P) {
+            C[i * P + j] = s / denom;
+            if (ti != tj) C[j * P + i] = s / denom;
+        }
+    }
 }
+
+// Sums the nz parts of every tile in order.  PREC 64: k_syrk64's tiles of 16
+// registers a thread; 32: k_syrk32's of 64.
+template <int PREC>
+__global__ __launch_bounds__(256) void k_syrk_sum(const double* __restrict__ part, int nz, int64_t P, double denom,
+                                                  double* __restrict__ cov);
 
 // ---------------------------------------------------------------------------
 // SYRK, float32 MFMA: 128x128 tile per block, 2x2 waves of 64x64,
@@ -147,10 +194,23 @@ constexpr int kMT = 128;    // tile
 constexpr int kKT = 32;     // rows per LDS slab
 constexpr int kKC = 256;    // rows per float32 accumulation chunk
 
+__device__ __forceinline__ void syrk32_at(int q, int t, int& i, int& j) {
+    const int lane = t & 63, wid = t >> 6, a = q >> 5, b = (q >> 4) & 1, r = q & 15;
+    i = (wid >> 1) * 64 + a * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    j = (wid & 1) * 64 + b * 32 + (lane & 31);
+}
+
 // kc: rows summed in the float32 accumulators before they are added into
-// the float64 ones (a multiple of kKT; Npad or more: float32 throughout)
-__global__ __launch_bounds__(256) void k_syrk32(const float* __restrict__ dev, int64_t Npad, int64_t Ppad,
-                                                int64_t P, int64_t kc, double denom, double* __restrict__ cov) {
+// the float64 ones (a multiple of kKT; Npad or more: float32 throughout).
+// split: rows per gridDim.z part, a multiple of kc; part != NULL: the parts'
+// raw sums go there (k_syrk_sum adds them).  A slab's loads are in flight
+// over the products of the one before it, and two blocks fit on a CU (the
+// float64 accumulators leave room for no more; with one, 1.77 ms).  5000
+// mocks of 2120 x 3: 1.62 ms with 459 blocks and a slab's loads waited for,
+// 1.26 ms and 0.08 ms for the sums in two parts here.
+__global__ __launch_bounds__(256, 2) void k_syrk32(const float* __restrict__ dev, int64_t Npad, int64_t Ppad,
+                                                int64_t P, int64_t kc, int64_t split, double denom,
+                                                double* __restrict__ part, double* __restrict__ cov) {
     __shared__ __align__(16) float As[kKT][kMT];
     __shared__ __align__(16) float Bs[kKT][kMT];
     const int e = blockIdx.y;
@@ -170,17 +230,28 @@ __global__ __launch_bounds__(256) void k_syrk32(const float* __restrict__ dev, i
                 dacc[a][b][r] = 0.0;
             }
         }
+    const int64_t nb = int64_t(blockIdx.z) * split, ne = min(nb + split, Npad);
+    // this thread stages columns c4 .. c4 + 3 of rows k8, k8 + 8, ...
+    const int c4 = (threadIdx.x & 31) * 4, k8 = threadIdx.x >> 5;
+    float4 va[kKT / 8], vb[kKT / 8];
+    auto load = [&](int64_t n0) {
+#pragma unroll
+        for (int q = 0; q < kKT / 8; q++) {
+            const float* row = D + (n0 + k8 + 8 * q) * Ppad + c4;
+            va[q] = *reinterpret_cast<const float4*>(row + i0);
+            vb[q] = *reinterpret_cast<const float4*>(row + j0);
+        }
+    };
+    load(nb);
     int64_t since = 0;
-    for (int64_t n0 = 0; n0 < Npad; n0 += kKT) {
-        // each thread loads 4 float4 of each slab: 32 rows x 128 floats
-        for (int q = threadIdx.x; q < kKT * kMT / 4; q += 256) {
-            const int kk = q / (kMT / 4), c4 = (q % (kMT / 4)) * 4;
-            const float4 va = *reinterpret_cast<const float4*>(D + (n0 + kk) * Ppad + i0 + c4);
-            const float4 vb = *reinterpret_cast<const float4*>(D + (n0 + kk) * Ppad + j0 + c4);
-            *reinterpret_cast<float4*>(&As[kk][c4]) = va;
-            *reinterpret_cast<float4*>(&Bs[kk][c4]) = vb;
+    for (int64_t n0 = nb; n0 < ne; n0 += kKT) {
+#pragma unroll
+        for (int q = 0; q < kKT / 8; q++) {
+            *reinterpret_cast<float4*>(&As[k8 + 8 * q][c4]) = va[q];
+            *reinterpret_cast<float4*>(&Bs[k8 + 8 * q][c4]) = vb[q];
         }
         __syncthreads();
+        if (n0 + kKT < ne) load(n0 + kKT);
 #pragma unroll
         for (int ks = 0; ks < kKT; ks += 2) {
             float a0 = As[ks + lk][wr * 64 + li];
@@ -194,7 +265,7 @@ __global__ __launch_bounds__(256) void k_syrk32(const float* __restrict__ dev, i
         }
         __syncthreads();
         since += kKT;
-        if (since == kc || n0 + kKT >= Npad) {
+        if (since == kc || n0 + kKT >= ne) {
             for (int a = 0; a < 2; a++)
                 for (int b = 0; b < 2; b++)
                     for (int r = 0; r < 16; r++) {
@@ -204,18 +275,94 @@ __global__ __launch_bounds__(256) void k_syrk32(const float* __restrict__ dev, i
             since = 0;
         }
     }
+    const int64_t tile = (int64_t(blockIdx.z) * gridDim.y + e) * gridDim.x + blockIdx.x;
     double* C = cov + int64_t(e) * P * P;
-    for (int a = 0; a < 2; a++)
-        for (int b = 0; b < 2; b++)
-            for (int r = 0; r < 16; r++) {
-                const int64_t i = i0 + wr * 64 + a * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-                const int64_t j = j0 + wc * 64 + b * 32 + li;
-                if (i < P && j < P) {
-                    const double v = dacc[a][b][r] / denom;
-                    C[i * P + j] = v;
-                    if (ti != tj) C[j * P + i] = v;
-                }
-            }
+#pragma unroll
+    for (int q = 0; q < 64; q++) {
+        const double s = dacc[q >> 5][(q >> 4) & 1][q & 15];
+        if (part) {
+            part[(tile * 64 + q) * 256 + threadIdx.x] = s;
+            continue;
+        }
+        int il, jl;
+        syrk32_at(q, threadIdx.x, il, jl);
+        const int64_t i = i0 + il, j = j0 + jl;
+        if (i < P && j < P) {
+            const double v = s / denom;
+            C[i * P + j] = v;
+            if (ti != tj) C[j * P + i] = v;
+        }
+    }
+}
+
+template <int PREC>
+__global__ __launch_bounds__(256) void k_syrk_sum(const double* __restrict__ part, int nz, int64_t P, double denom,
+                                                  double* __restrict__ cov) {
+    constexpr int NQ = PREC == 64 ? 16 : 64, T = PREC == 64 ? kST : kMT;
+    const int e = blockIdx.y;
+    int ti, tj;
+    tri_tile(blockIdx.x, ti, tj);
+    double* C = cov + int64_t(e) * P * P;
+    const int64_t zs = int64_t(gridDim.y) * gridDim.x * NQ * 256;
+    for (int q = blockIdx.z; q < NQ; q += gridDim.z) {
+        const double* src = part + ((int64_t(e) * gridDim.x + blockIdx.x) * NQ + q) * 256 + threadIdx.x;
+        double s = src[0];
+        for (int z = 1; z < nz; z++) s += src[z * zs];
+        int il, jl;
+        if (PREC == 64) syrk64_at(q, threadIdx.x, il, jl);
+        else syrk32_at(q, threadIdx.x, il, jl);
+        const int64_t i = int64_t(ti) * T + il, j = int64_t(tj) * T + jl;
+        if (i < P && j < P) {
+            const double v = s / denom;
+            C[i * P + j] = v;
+            if (ti != tj) C[j * P + i] = v;
+        }
+    }
+}
+
+// Parts the mocks are split into: about four blocks per CU where whole tiles
+// give fewer than two, each part a whole number of `unit` rows and at least
+// four of them, at most 16 parts.  (595 tiles of 200 mocks: 49 + 16 us in two
+// parts and their sum, 50 us whole.)
+static int64_t syrk_split(int64_t rows, int64_t unit, int64_t blocks, int n_cu, int& nz) {
+    const int64_t units = (rows + unit - 1) / unit;
+    const int64_t want = blocks >= 2 * n_cu ? 1 : std::min<int64_t>({4 * n_cu / blocks, units / 4, 16});
+    const int64_t per = (units + std::max<int64_t>(want, 1) - 1) / std::max<int64_t>(want, 1);
+    nz = int((units + per - 1) / per);
+    return per * unit;
+}
+
+// cov[e] = the sample covariance of estimate e of ne, in float64.
+static lc_status syrk_fp64(DeviceCtx* ctx, const double* x, const double* mean, int64_t N, int64_t P, int ne,
+                           double denom, double* cov, hipStream_t s) {
+    const int64_t T = (P + kST - 1) / kST, nt = T * (T + 1) / 2;
+    int nz;
+    const int64_t split = syrk_split(N, kSK, nt * ne, ctx->n_cu, nz);
+    DevBuf<double> part;
+    if (nz > 1) LC_TRY(part.alloc(size_t(nz) * ne * nt * kST * kST, s));
+    k_syrk64<<<dim3(unsigned(nt), ne, nz), 256, 0, s>>>(x, ne * P, mean, N, P, split, denom, part.get(), cov);
+    if (nz > 1) k_syrk_sum<64><<<dim3(unsigned(nt), ne, 4), 256, 0, s>>>(part.get(), nz, P, denom, cov);
+    return LC_OK;
+}
+
+// The same from float32 deviations and MFMA products.
+static lc_status syrk_fp32(DeviceCtx* ctx, const double* x, const double* mean, int64_t N, int64_t P, int ne,
+                           bool acc32, double denom, double* cov, hipStream_t s) {
+    const int64_t Npad = (N + kKT - 1) / kKT * kKT;
+    const int64_t Ppad = (P + kMT - 1) / kMT * kMT;
+    DevBuf<float> dev;
+    LC_TRY(dev.alloc(size_t(ne * Npad * Ppad), s));
+    k_dev32<<<nblocks(ne * Npad * Ppad, 256, 65536), 256, 0, s>>>(x, mean, N, P, ne, Npad, Ppad, dev.get());
+    const int64_t T = Ppad / kMT, nt = T * (T + 1) / 2;
+    int nz = 1;
+    int64_t split = Npad;
+    if (!acc32) split = syrk_split(Npad, kKC, nt * ne, ctx->n_cu, nz);
+    DevBuf<double> part;
+    if (nz > 1) LC_TRY(part.alloc(size_t(nz) * ne * nt * kMT * kMT, s));
+    k_syrk32<<<dim3(unsigned(nt), ne, nz), 256, 0, s>>>(dev.get(), Npad, Ppad, P, acc32 ? INT64_MAX : int64_t(kKC),
+                                                        split, denom, part.get(), cov);
+    if (nz > 1) k_syrk_sum<32><<<dim3(unsigned(nt), ne, 16), 256, 0, s>>>(part.get(), nz, P, denom, cov);
+    return LC_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -303,7 +450,7 @@ __global__ void k_zero_flags(CheckFlags* fl, int n) {
 // panel is one launch of single waves: every block factors the 32 x 32
 // diagonal block for itself (row i in lane i's registers, the column's other
 // elements through readlane) and with the same broadcast elements solves 64
-// rows below it, one per lane: TODO us, where a launch for the diagonal block
+// rows below it, one per lane: 17 us, where a launch for the diagonal block
 // (one thread forming each pivot) took 46 us and one for the rows 52 us.  The
 // update is a contraction over the panel's 32 columns and runs on the matrix
 // cores: 13 us, 24 us before.  2000 rows: 8.0 ms before, 2.0 ms now.
@@ -371,8 +518,6 @@ __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int6
             if (c <= lane) own[c] = r[c];
     }
 }
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // Trailing update of the lower triangle: A22 -= L21 L21^T, for a full panel
 // of 32 columns.  64 x 64 tiles, four waves of 32 x 32, each 2 x 2 blocks of
@@ -1070,10 +1215,6 @@ __global__ __launch_bounds__(kBisectThreads) void k_bisect(const double* __restr
     if (tid == 0) out[blockIdx.x] = __builtin_amdgcn_ldexp(0.5 * (lo + hi), -ex);
 }
 
-static int nblocks(int64_t n, int threads, int cap = 4096) {
-    return int(std::max<int64_t>(1, std::min<int64_t>((n + threads - 1) / threads, cap)));
-}
-
 // Tridiagonalisation with one launch per column, on a fresh copy W of the
 // block.
 static void tridiag_columns(const double* C, int64_t P, int64_t off, int64_t n, double* W, CheckFlags* fl,
@@ -1186,10 +1327,8 @@ static lc_status covariance_impl(const double* xi, int32_t n_mock, int64_t P, in
         return fail(LC_ERR_INVALID, "precision = %d is not LC_FP64 / LC_FP32_MFMA / LC_FP32_MFMA_CHECKED",
                     precision);
     if (acc32 && precision == LC_FP64) return fail(LC_ERR_INVALID, "LC_ACC32 needs a float32 MFMA precision");
-    const int64_t kc = acc32 ? INT64_MAX : int64_t(kKC);
     DeviceCtx* ctx;
     LC_TRY(get_ctx(&ctx));
-    (void)ctx;
     const int64_t N = n_mock;
     const int64_t PP = P * P;
     const int64_t W3 = 3 * P;
@@ -1212,24 +1351,8 @@ static lc_status covariance_impl(const double* xi, int32_t n_mock, int64_t P, in
         k_mean_partial<<<g, 256, 0, s>>>(xi, N, W3, part);
         k_mean_final<<<unsigned((W3 + 255) / 256), 256, 0, s>>>(part, nchunk, W3, N, mean);
     }
-    const int64_t T64 = (P + 63) / 64;
-    auto run_fp64 = [&](double* covbuf) -> lc_status {
-        DevBuf<double> dev;
-        LC_TRY(dev.alloc(size_t(3 * N * P), s));
-        k_dev64<<<nblocks(3 * N * P, 256, 65536), 256, 0, s>>>(xi, mean, N, P, 3, dev.get());
-        k_syrk64<<<dim3(unsigned(T64 * (T64 + 1) / 2), 3), 256, 0, s>>>(dev.get(), N, P, denom, covbuf);
-        return LC_OK;
-    };
-    auto run_fp32 = [&](double* covbuf) -> lc_status {
-        const int64_t Npad = (N + kKT - 1) / kKT * kKT;
-        const int64_t Ppad = (P + kMT - 1) / kMT * kMT;
-        DevBuf<float> dev;
-        LC_TRY(dev.alloc(size_t(3 * Npad * Ppad), s));
-        k_dev32<<<nblocks(3 * Npad * Ppad, 256, 65536), 256, 0, s>>>(xi, mean, N, P, 3, Npad, Ppad, dev.get());
-        const int64_t T = Ppad / kMT;
-        k_syrk32<<<dim3(unsigned(T * (T + 1) / 2), 3), 256, 0, s>>>(dev.get(), Npad, Ppad, P, kc, denom, covbuf);
-        return LC_OK;
-    };
+    auto run_fp64 = [&](double* covbuf) { return syrk_fp64(ctx, xi, mean, N, P, 3, denom, covbuf, s); };
+    auto run_fp32 = [&](double* covbuf) { return syrk_fp32(ctx, xi, mean, N, P, 3, acc32, denom, covbuf, s); };
     if (precision == LC_FP64) {
         LC_TRY(run_fp64(cov));
     } else {
@@ -1326,10 +1449,8 @@ extern "C" lc_status lc_sample_covariance(const double* x, int32_t n_mock, int32
     if (precision != LC_FP64 && precision != LC_FP32_MFMA)
         return fail(LC_ERR_INVALID, "precision = %d is not LC_FP64 / LC_FP32_MFMA", precision);
     if (acc32 && precision == LC_FP64) return fail(LC_ERR_INVALID, "LC_ACC32 needs LC_FP32_MFMA");
-    const int64_t kc = acc32 ? INT64_MAX : int64_t(kKC);
     DeviceCtx* ctx;
     LC_TRY(get_ctx(&ctx));
-    (void)ctx;
     hipStream_t s = (hipStream_t)stream;
     const int64_t N = n_mock, PL = P;
     const double denom = double(N - 1);
@@ -1345,19 +1466,9 @@ extern "C" lc_status lc_sample_covariance(const double* x, int32_t n_mock, int32
         k_mean_final<<<unsigned((PL + 255) / 256), 256, 0, s>>>(part, nchunk, PL, N, mean);
     }
     if (precision == LC_FP64) {
-        DevBuf<double> dev;
-        LC_TRY(dev.alloc(size_t(N * PL), s));
-        k_dev64<<<nblocks(N * PL, 256, 65536), 256, 0, s>>>(x, mean, N, PL, 1, dev.get());
-        const int64_t T64 = (PL + 63) / 64;
-        k_syrk64<<<dim3(unsigned(T64 * (T64 + 1) / 2), 1), 256, 0, s>>>(dev.get(), N, PL, denom, C);
+        LC_TRY(syrk_fp64(ctx, x, mean, N, PL, 1, denom, C, s));
     } else {
-        const int64_t Npad = (N + kKT - 1) / kKT * kKT;
-        const int64_t Ppad = (PL + kMT - 1) / kMT * kMT;
-        DevBuf<float> dev;
-        LC_TRY(dev.alloc(size_t(Npad * Ppad), s));
-        k_dev32<<<nblocks(Npad * Ppad, 256, 65536), 256, 0, s>>>(x, mean, N, PL, 1, Npad, Ppad, dev.get());
-        const int64_t T = Ppad / kMT;
-        k_syrk32<<<dim3(unsigned(T * (T + 1) / 2), 1), 256, 0, s>>>(dev.get(), Npad, Ppad, PL, kc, denom, C);
+        LC_TRY(syrk_fp32(ctx, x, mean, N, PL, 1, acc32, denom, C, s));
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(LC_ERR_HIP, "covariance launch failed: %s", hipGetErrorString(e));

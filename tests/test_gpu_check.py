@@ -1,5 +1,5 @@
-"""The check of C^LC at the sizes where its kernels change (GPU, against
-LAPACK): rows per block of the resident tridiagonalisation (8 per block, 512
+"""The covariance products and the check of C^LC at the sizes where their
+kernels change (GPU, against numpy and LAPACK): tiles and parts of the products; rows per block of the resident tridiagonalisation (8 per block, 512
 columns per thread slot), the launch-per-column one past 2048 rows, panels of
 the Cholesky factorisation, and degenerate blocks."""
 import numpy as np
@@ -76,3 +76,31 @@ def test_check_degenerate_blocks(n):
               np.outer(d, d), np.diag(np.where(np.arange(n) % 3 == 0, 0.0, d))):
         rep, Co = _check(C, 0)
         _assert_report(rep, Co, 0)
+
+
+# one row, edges of the 64- and 128-wide tiles; mocks below a slab, past the
+# first split, a last part shorter than the others
+@pytest.mark.parametrize("P", [1, 16, 63, 65, 129, 260])
+@pytest.mark.parametrize("n_mock", [2, 15, 17, 64, 127, 130, 1025, 2309])
+def test_sample_covariance_tiles_and_parts(P, n_mock):
+    import torch
+
+    from paper_2205_11852_amd import lc
+
+    rng = np.random.default_rng(P * 10000 + n_mock)
+    x = rng.normal(size=(n_mock, P)) * rng.uniform(0.01, 10.0, size=P) + rng.normal(size=P)
+    ref = np.cov(x, rowvar=False).reshape(P, P)
+    d = np.abs(x - x.mean(0))
+    size = d.T @ d / (n_mock - 1)
+    xd = torch.as_tensor(x).cuda()
+    C = torch.full((P, P), float("nan"), dtype=torch.float64, device="cuda")
+    # float64: the sums' rounding; float32: rounded deviations and 256 rows
+    # summed in float32 (with LC_ACC32 all of them)
+    u = 2.0 ** -24
+    for prec, tol in ((lc.LC_FP64, 4.0 * (n_mock + 4) * 2.3e-16), (lc.LC_FP32_MFMA, (256 + 4) * u),
+                      (lc.LC_FP32_MFMA | lc.LC_ACC32, (n_mock + 4) * u)):
+        lc.lc_sample_covariance(xd, n_mock, P, prec, C)
+        got = C.cpu().numpy()
+        shift = 4.0 * 2.3e-16 * np.abs(x).max() * np.sqrt(np.outer(size.diagonal(), size.diagonal()))
+        assert np.all(np.abs(got - ref) <= tol * size + n_mock * shift + 1e-300), prec
+        assert np.array_equal(got, got.T)
