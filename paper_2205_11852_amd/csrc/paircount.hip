@@ -1174,10 +1174,11 @@ static float f32_down(double v) {  // largest float <= v
 // items per box task half empty (64 mocks of 1e5: 79.0 -> 76.4 ms).  What
 // speaks for larger items is the cost of one: a pop, two barriers and, since
 // consecutive items of a queue go to different blocks, often a flush of the
-// histogram.  So a cell stands alone when its expected candidate tests pay
-// for that (below kRowTests, runs of cells up to a row: (r_p, pi) counts of
-// 3.5e4 tests per cell run 2.67 ms in pairs of cells, 2.75-2.83 ms singly),
-// unless that would leave fewer than two items per slot; and it is cut into
+// histogram.  So cells form runs, up to a row, where their expected candidate
+// tests do not pay for an item (kRowTests: (r_p, pi) counts of 3.5e4 tests
+// per cell run 2.67 ms in pairs of cells, 2.75-2.83 ms singly) and where more
+// than 64 items per slot would be left (1000 box mocks keep their rows),
+// unless that would leave fewer than two items per slot; and a cell is cut into
 // slices of at least kSliceTests while there are fewer than eight items per
 // slot.  More than 8 slices gain nothing (the waves' last, partly filled
 // j blocks grow in number: 16 slices of the single DD 0.57 ms).
@@ -1193,7 +1194,8 @@ static void split_items(PcParams& p, const GridGeom& g, const lc_tuning* tune, b
     if (tune && tune->cells_per_item > 0) {
         cpi = tune->cells_per_item;
     } else if (!per_task) {
-        const double run = std::min(kRowTests / std::max(tests, 1.0), cells / (2.0 * slots));
+        const double run = std::min(std::max(kRowTests / std::max(tests, 1.0), cells / (64.0 * slots)),
+                                    cells / (2.0 * slots));
         // (the queue indexes items with 31 bits)
         cpi = int64_t(std::min(double(g.n[0]), std::max({1.0, run, std::ceil(cells / double(1 << 30))})));
         if (cpi == 1) slices = std::llround(std::max(1.0, std::min({8.0, 8.0 * slots / cells, tests / kSliceTests})));
