@@ -9,7 +9,7 @@
 //       C = A + B/M                                    (float64)
 //   ->  Cholesky and eigenvalue extremes of each block of C (float64).
 //
-// The products D^T D run either in float64 (VALU) or as float32 MFMA
+// The products D^T D run as float64 MFMA (v_mfma_f64_16x16x4) or float32 MFMA
 // (v_mfma_f32_32x32x2f32) with float32 accumulation, by default over chunks
 // of 256 mocks whose partial sums are added in float64 (LC_ACC32: over all
 // mocks in float32).
