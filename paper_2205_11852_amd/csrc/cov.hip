@@ -468,8 +468,11 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
     return r * fma(-0.5 * d * r, r, 1.5);
 }
 
-// Columns [k0, k0 + nb) of L from the updated W: the diagonal block and the
-// rows below it, 64 per block (block 0 also stores the diagonal block).
+// Columns [k0, k0 + nb) of L from the updated W: the rows below the diagonal
+// block, 64 per block.  Every block reads the diagonal block, and blocks start
+// at any time (one after another where other work holds the CUs), so none may
+// store its factor over it: the factor stays in registers, and nothing after
+// this launch reads the diagonal block again.
 // FULL: nb = 32; the last panel may be narrower and has no rows below it.
 template <bool FULL>
 __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int64_t n, int64_t k0, int nb,
@@ -480,7 +483,7 @@ __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int6
     // columns past nb: identity)
     const int li = lane & (kNB - 1);
     double r[kNB], x[kNB];
-    double* const own = W + (k0 + (FULL || li < nb ? li : 0)) * n + k0;
+    const double* const own = W + (k0 + (FULL || li < nb ? li : 0)) * n + k0;
 #pragma unroll
     for (int c = 0; c < kNB; c++) r[c] = FULL || (li < nb && c < nb) ? own[c] : (li == c ? 1.0 : 0.0);
     // this lane's row below (past the last one, the last one again)
@@ -511,11 +514,6 @@ __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int6
     if (FULL && row < n) {
 #pragma unroll
         for (int c = 0; c < kNB; c++) dst[c] = x[c];
-    }
-    if (blockIdx.x == 0 && lane < nb) {
-#pragma unroll
-        for (int c = 0; c < kNB; c++)
-            if (c <= lane) own[c] = r[c];
     }
 }
 
