@@ -15,6 +15,7 @@
 // mocks in float32).
 #include <algorithm>
 #include <cfloat>
+#include <chrono>
 #include <cmath>
 #include <vector>
 
@@ -814,13 +815,17 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 8 : 4))) void k_hh_column(double
 //
 // Blocks that are not all resident at once (other work holds the CUs) would
 // wait for each other; every wait is bounded by `spin` polls, after which the
-// block raises *gave_up and ends, the others follow, and the caller goes
-// through the columns launch by launch.
+// block raises *gave_up and ends.  The others look at it as they start and
+// while they poll, and end too, and the caller goes through the columns launch
+// by launch.
 // ---------------------------------------------------------------------------
 constexpr int kTrThreads = 512;
 constexpr int kTrRows = 8;
 constexpr int kTrMaxBlocks = 256;
-constexpr int kTrSpin = 40000;   // some tens of milliseconds
+constexpr int kColumnUs = 12;    // a launch per column takes about this long per row
+// Polls of a wait, about 1.2 us each: no longer than the columns would take.
+constexpr int kTrSpinRow = 10, kTrSpinMin = 1000;
+constexpr int kTrLook = 32;      // polls from one look at *gave_up to the next
 constexpr unsigned long long kTrEmpty = 0x7FF4DEAD5EED0001ull;  // a NaN no operation returns
 
 // x plus the lane's neighbour under a DPP control (0 where there is none)
@@ -897,6 +902,7 @@ __global__ void k_tr_empty(unsigned long long* __restrict__ q, int64_t n, int* _
 
 // E columns per thread (n <= 512 E).  C: the block at (off, off) of a matrix
 // of row length P.  q: [3][2][n] slots (p, then the next row's elements).
+// spin = 0: every block gives up at its first column.
 // Element i of a thread's column c < k (reflected already) is kept zero.
 template <int E>
 __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restrict__ C, int64_t P, int64_t off, int n,
@@ -910,7 +916,7 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
     __shared__ double rnext[R];       // A[r][k+1] at the block's rows
     __shared__ double at_k[3], at_k1; // v, p and A[k][k] at k; x at k + 1
     __shared__ int failed;
-    if (fl->nan_seen) return;
+    if (fl->nan_seen || __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = blockIdx.x, B = gridDim.x;
     const int rlast = b + (n - 1 - b) / B * B;  // the block's last row
@@ -963,6 +969,9 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
 #pragma unroll
                 for (int u = 0; u < E; u++) ok = ok && sp[u] != kTrEmpty && sa[u] != kTrEmpty;
                 if (ok || polls >= spin) break;
+                if (polls % kTrLook == kTrLook - 1 &&
+                    __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                    break;
 #pragma unroll
                 for (int u = 0; u < E; u++) {
                     const int c = tid + u * kTrThreads;
@@ -970,7 +979,7 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
                     if (sa[u] == kTrEmpty) sa[u] = tr_get(qp + n + c);
                 }
             }
-            if (!ok) failed = 1;
+            if (!ok || spin == 0) failed = 1;
 #pragma unroll
             for (int u = 0; u < E; u++) {
                 w[u] = __longlong_as_double((long long)sp[u]);  // p for now
@@ -1233,9 +1242,51 @@ static void tridiag_columns(const double* C, int64_t P, int64_t off, int64_t n, 
     k_hh_tail<<<1, 256, 0, s>>>(W, n, q, d, e);
 }
 
+// A call's share of the blocks that this process has running in resident
+// tridiagonalisations on the device, a CU each; given back when the call ends.
+// Checks of several threads whose blocks do not fit on the card together would
+// hold each other up (four of 2000 rows: up to 99 ms each until they gave up;
+// a launch per column 55 ms; one after another 13 to 44 ms), so a call waits
+// in line for its share, at most twice as long as its own columns would take.
+class ResidentBlocks {
+  public:
+    explicit ResidentBlocks(DeviceCtx* ctx) : ctx_(ctx) {}
+    ~ResidentBlocks() {
+        if (!n_) return;
+        {
+            std::lock_guard<std::mutex> lk(ctx_->resident_mu);
+            ctx_->resident_blocks -= n_;
+        }
+        ctx_->resident_cv.notify_all();
+    }
+    ResidentBlocks(const ResidentBlocks&) = delete;
+    ResidentBlocks& operator=(const ResidentBlocks&) = delete;
+    bool take(int n, std::chrono::microseconds wait) {
+        std::unique_lock<std::mutex> lk(ctx_->resident_mu);
+        std::list<const ResidentBlocks*>& line = ctx_->resident_line;
+        line.push_back(this);
+        const bool got = ctx_->resident_cv.wait_for(
+            lk, wait, [&] { return line.front() == this && ctx_->resident_blocks + n <= ctx_->n_cu; });
+        line.remove(this);
+        if (got) ctx_->resident_blocks += n_ = n;
+        lk.unlock();
+        ctx_->resident_cv.notify_all();  // the next in line
+        return got;
+    }
+
+  private:
+    DeviceCtx* ctx_;
+    int n_ = 0;
+};
+
 // Check one diagonal block [off, off+n) of C.  Writes chol_ok, n_neg, min, max.
-static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n, hipStream_t s,
-                             int32_t* chol_ok, int32_t* n_neg, double* mn, double* mx) {
+// spin: polls a wait of the resident tridiagonalisation may take (kTrDefault:
+// by the rows; kTrColumns: a launch per column instead); *gave_up (if given):
+// it ran and gave up.
+constexpr int kTrDefault = -1, kTrColumns = -2;
+static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n, hipStream_t s, int spin,
+                             int32_t* chol_ok, int32_t* n_neg, double* mn, double* mx, int32_t* gave_up_out) {
+    if (gave_up_out) *gave_up_out = 0;
     if (n == 0) {  // an empty block: nothing to factor, no eigenvalues
         *chol_ok = 1;
         *n_neg = 0;
@@ -1280,14 +1331,17 @@ static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n,
     DevBuf<unsigned long long> slots;
     DeviceCtx* ctx;
     LC_TRY(get_ctx(&ctx));
-    const bool resident = n <= int64_t(kTrRows) * std::min(kTrMaxBlocks, ctx->n_cu) && n <= 4 * kTrThreads;
+    const int B = int((n + kTrRows - 1) / kTrRows);
+    bool resident = spin != kTrColumns && B <= std::min(kTrMaxBlocks, ctx->n_cu) && n <= 4 * kTrThreads;
+    ResidentBlocks held(ctx);
+    if (resident) resident = held.take(B, std::chrono::microseconds(2 * kColumnUs * n));
     if (resident) {
         LC_TRY(slots.alloc(size_t(6 * n) + 1, s));
         int* const gave_up = reinterpret_cast<int*>(slots.get() + 6 * n);
         k_tr_empty<<<nblocks(6 * n, 256), 256, 0, s>>>(slots.get(), 6 * n, gave_up);
-        const unsigned B = unsigned((n + kTrRows - 1) / kTrRows);
+        if (spin == kTrDefault) spin = std::max(kTrSpinMin, kTrSpinRow * int(n));
         auto* kern = n <= kTrThreads ? k_tridiag<1> : n <= 2 * kTrThreads ? k_tridiag<2> : k_tridiag<4>;
-        kern<<<B, kTrThreads, 0, s>>>(C, P, off, int(n), fl, slots.get(), kTrSpin, gave_up, d, e);
+        kern<<<unsigned(B), kTrThreads, 0, s>>>(C, P, off, int(n), fl, slots.get(), spin, gave_up, d, e);
     } else {
         tridiag_columns(C, P, off, n, W, fl, v, pv, vpp, tau, d, e, s);
     }
@@ -1299,6 +1353,7 @@ static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n,
     LC_TRY_HIP(hipMemcpyAsync(&hf, fl, sizeof hf, hipMemcpyDeviceToHost, s));
     LC_TRY_HIP(hipMemcpyAsync(hr, res, sizeof hr, hipMemcpyDeviceToHost, s));
     LC_TRY_HIP(hipStreamSynchronize(s));
+    if (gave_up_out) *gave_up_out = hg;
     if (hg) {
         // the blocks were not all resident: column by column instead
         tridiag_columns(C, P, off, n, W, fl, v, pv, vpp, tau, d, e, s);
@@ -1310,6 +1365,15 @@ static lc_status check_block(const double* C, int64_t P, int64_t off, int64_t n,
     *n_neg = int32_t(hr[2]);
     *mn = hr[0];
     *mx = hr[1];
+    return LC_OK;
+}
+
+// Both blocks [0, split) and [split, P) of C.
+static lc_status check_blocks(const double* C, int64_t P, int64_t split, hipStream_t s, int spin, lc_cov_report* rep,
+                              int32_t* gave_up) {
+    for (int q = 0; q < 2; q++)
+        LC_TRY(check_block(C, P, q ? split : 0, q ? P - split : split, s, spin, &rep->chol_ok[q], &rep->n_neg_eig[q],
+                           &rep->min_eig[q], &rep->max_eig[q], gave_up ? gave_up + q : nullptr));
     return LC_OK;
 }
 
@@ -1396,14 +1460,10 @@ static lc_status covariance_impl(const double* xi, int32_t n_mock, int64_t P, in
         rep->rel_frob_vs_fp64[0] = rel[0];
         rep->rel_frob_vs_fp64[1] = rel[1];
         rep->rel_frob_vs_fp64[2] = rel[2];
-        LC_TRY(check_block(C, P, 0, split, s, &rep->chol_ok[0], &rep->n_neg_eig[0], &rep->min_eig[0],
-                           &rep->max_eig[0]));
-        LC_TRY(check_block(C, P, split, P - split, s, &rep->chol_ok[1], &rep->n_neg_eig[1], &rep->min_eig[1],
-                           &rep->max_eig[1]));
+        LC_TRY(check_blocks(C, P, split, s, kTrDefault, rep, nullptr));
     }
     return LC_OK;
 }
-
 
 }  // namespace lc
 
@@ -1471,4 +1531,18 @@ extern "C" lc_status lc_sample_covariance(const double* x, int32_t n_mock, int32
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(LC_ERR_HIP, "covariance launch failed: %s", hipGetErrorString(e));
     return LC_OK;
+}
+
+// Testing (not part of lc.h): the check alone, of a device matrix C, with the
+// wait bound of its resident tridiagonalisation: spin > 0 polls; 0, it gives up
+// at its first column; -1, as lc_covariance; -2, a launch per column.
+// gave_up: HOST [2], per block.
+extern "C" lc_status lc_testing_check(const double* C, int32_t P, int32_t n_split, int32_t spin, lc_cov_report* rep,
+                                      int32_t* gave_up, void* stream) {
+    clear_error();
+    if (!C || !rep || !gave_up) return fail(LC_ERR_INVALID, "NULL argument");
+    if (P < 1 || P > 4 * LC_MAX_BINS || n_split < 0 || n_split > P || spin < kTrColumns)
+        return fail(LC_ERR_INVALID, "P = %d, n_split = %d or spin = %d out of range", P, n_split, spin);
+    for (double& r : rep->rel_frob_vs_fp64) r = -1.0;
+    return check_blocks(C, P, n_split, (hipStream_t)stream, spin, rep, gave_up);
 }

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
@@ -67,6 +68,8 @@ struct ScratchBlock {
     bool idle = true;
 };
 
+class ResidentBlocks;
+
 struct DeviceCtx {
     int device = -1;
     int n_cu = 0;
@@ -74,6 +77,10 @@ struct DeviceCtx {
     std::mutex mu;                      // guards the pinned ring
     PinnedSlot pinned[kPinnedSlots];
     int pinned_next = 0;
+    std::mutex resident_mu;             // guards the next three
+    std::condition_variable resident_cv;
+    int resident_blocks = 0;            // blocks of the resident tridiagonalisations under way
+    std::list<const ResidentBlocks*> resident_line;  // calls that wait to start theirs
     std::mutex scratch_mu;              // guards the scratch cache
     std::list<ScratchBlock> scratch;    // freed buffers, oldest first
     size_t scratch_bytes = 0;           // their sum

@@ -1,0 +1,125 @@
+"""Both ways of the check's tridiagonalisation, and the way from one to the
+other (GPU, against LAPACK): matrices handed to the check as they are, with the
+wait bound of the resident kernel given, or a launch per column."""
+import ctypes
+import threading
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+DEFAULT, COLUMNS = -1, -2
+
+
+def check(C, n_split=0, spin=DEFAULT, stream=None):
+    """Report and the blocks' give-up marks; C is a device matrix."""
+    import torch
+
+    from paper_2205_11852_amd import lc
+
+    rep, gave = lc.lc_cov_report(), (ctypes.c_int32 * 2)()
+    s = stream if stream is not None else torch.cuda.current_stream()
+    rc = lc.lib().lc_testing_check(ctypes.c_void_p(C.data_ptr()), C.shape[0], n_split, spin, ctypes.byref(rep), gave,
+                                   ctypes.c_void_p(s.cuda_stream))
+    assert rc == 0, lc.last_error()
+    return rep.as_dict(), list(gave)
+
+
+def device(C):
+    import torch
+
+    return torch.as_tensor(np.ascontiguousarray(C)).cuda()
+
+
+def assert_spectrum(rep, C, blk=1):
+    w = np.linalg.eigvalsh(C)
+    # backward stable: an error of a few n eps of the largest
+    tol = 20 * len(w) * 2.3e-16 * max(abs(w[0]), abs(w[-1]))
+    assert abs(rep["min_eig"][blk] - w[0]) <= tol and abs(rep["max_eig"][blk] - w[-1]) <= tol
+    assert (w < -tol).sum() <= rep["n_neg_eig"][blk] <= (w <= tol).sum()
+    if w[0] > tol:
+        assert rep["chol_ok"][blk] == 1
+    if w[0] < -tol:
+        assert rep["chol_ok"][blk] == 0
+
+
+def dense(n, seed, shift):
+    rng = np.random.default_rng(seed)
+    X = rng.normal(size=(n, n + 50)) * rng.uniform(0.1, 3.0, size=(n, 1))
+    C = X @ X.T / n
+    return 0.5 * (C + C.T) - shift * np.eye(n)
+
+
+# the column kernel's switches: 256 trailing rows, 512 and 1024 held elements;
+# the resident one's: rows per block, 512 and 1024 columns
+SIZES = [1, 2, 3, 4, 5, 8, 9, 17, 65, 256, 258, 259, 298, 513, 514, 1025, 1083]
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("shift", [0.0, 1.0])
+def test_launch_per_column(n, shift):
+    C = dense(n, n, shift)
+    rep, gave = check(device(C), spin=COLUMNS)
+    assert gave == [0, 0]
+    assert_spectrum(rep, C)
+
+
+@pytest.mark.parametrize("n", SIZES + [2000, 2048])
+def test_resident_gives_up(n):
+    """Bound 0: every block gives up at its first column (a block of one row
+    has none) and the columns take over."""
+    C = dense(n, n, 0.5)
+    rep, gave = check(device(C), spin=0)
+    assert gave == [0, int(n > 1)]
+    assert_spectrum(rep, C)
+
+
+@pytest.mark.parametrize("spin", [1, 2, 5, 40])
+@pytest.mark.parametrize("n", [9, 65, 600, 2000])
+def test_short_waits(n, spin):
+    """Some blocks may give up in the middle while others still wait."""
+    C = dense(n, n, 0.5)
+    d = device(C)
+    for _ in range(3):
+        rep, _ = check(d, spin=spin)
+        assert_spectrum(rep, C)
+
+
+def test_two_blocks_through_both():
+    C = dense(700, 7, 0.3)
+    d = device(C)
+    for spin in (DEFAULT, COLUMNS, 0):
+        rep, gave = check(d, 130, spin)
+        assert gave == ([1, 1] if spin == 0 else [0, 0])
+        assert_spectrum(rep, C[:130, :130], 0)
+        assert_spectrum(rep, C[130:, 130:], 1)
+
+
+def test_checks_of_several_threads():
+    """Their resident blocks do not fit on the card together."""
+    import torch
+
+    C = dense(2000, 11, 0.5)
+    d = device(C)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    out, bar = [None] * 4, threading.Barrier(4)
+
+    def work(i):
+        torch.cuda.set_device(0)
+        bar.wait()
+        out[i] = [check(d, stream=streams[i])[0] for _ in range(2)]
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert_spectrum(out[0][0], C)
+    for o in out:
+        for rep in o:
+            for k in ("chol_ok", "n_neg_eig"):
+                assert rep[k] == out[0][0][k]
+            assert np.allclose(rep["min_eig"][1], out[0][0]["min_eig"][1], atol=1e-11)
+            assert np.allclose(rep["max_eig"][1], out[0][0]["max_eig"][1], rtol=1e-11)
