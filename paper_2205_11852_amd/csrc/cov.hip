@@ -623,6 +623,24 @@ __device__ __forceinline__ HhVW hh_vw(const HhPending& q, double K, int64_t i) {
     return HhVW{v, q.p[i] - K * v};
 }
 
+// Reflection of x onto alpha e1 from its first element and the squares of the
+// others, summed apart from its own: elements below 1e-8 of the first one
+// would vanish in the rounding of |x|^2, and with them the coupling they carry.
+struct HhReflect {
+    double e;     // the off-diagonal entry: alpha, or x0 where there is nothing to reflect
+    double v0;    // v = (v0, x1, x2, ...)
+    double tau;
+    bool trivial;
+};
+__device__ __forceinline__ HhReflect hh_reflect(double x0, double rest2) {
+    const double nrm = sqrt(x0 * x0 + rest2);
+    const double alpha = x0 > 0 ? -nrm : nrm;
+    const double v0 = x0 - alpha, vnorm2 = rest2 + v0 * v0;
+    const bool trivial = !(rest2 > 0.0) || !(vnorm2 >= DBL_MIN);  // (2 / vnorm2 stays finite)
+    // (a NaN among the others, from infinities, shows in e)
+    return HhReflect{trivial ? x0 + 0.0 * rest2 : alpha, v0, trivial ? 0.0 : 2.0 / vnorm2, trivial};
+}
+
 constexpr int kHhRows = 4;  // rows of A22 per k_hh_column block
 
 // WAVES waves per row: 4 while the trailing matrix is large (more loads in
@@ -698,28 +716,23 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 8 : 4))) void k_hh_column(double
 #pragma unroll
     for (int t = 0; t < NPF; t++) {
         const double x = xk(nr[t], nv[t], np[t]);
-        s += x * x;
+        s += t == 0 && threadIdx.x == 0 ? 0.0 : x * x;
     }
 #pragma unroll 2
     for (int64_t j = threadIdx.x + int64_t(NPF) * NT; j < m; j += NT) {
         const double x = xk(row[j], pv_at(j + 1), pp_at(j + 1));
         s += x * x;
     }
-    const double norm2 = block_sum(s, red);
-    const double x0 = xk(x0r, x0v, x0p);
-    const double nrm = sqrt(norm2);
-    const double alpha = x0 > 0 ? -nrm : nrm;   // reflect x onto alpha * e1
-    const double v0 = x0 - alpha;
-    const double vnorm2 = norm2 - x0 * x0 + v0 * v0;
-    const bool trivial = !(vnorm2 > 0.0) || (norm2 - x0 * x0) <= 0.0;
-    const double t = trivial ? 0.0 : 2.0 / vnorm2;
+    const HhReflect h = hh_reflect(xk(x0r, x0v, x0p), block_sum(s, red));
+    const bool trivial = h.trivial;
+    const double v0 = h.v0, t = h.tau;
     if (blockIdx.x == 0) {
         for (int64_t i = threadIdx.x; i < m; i += NT)
             v[i] = trivial ? 0.0 : (i == 0 ? v0 : xk(row[i], pv_at(i + 1), pp_at(i + 1)));
         if (threadIdx.x == 0) {
             // diagonal entry k: the old one less 2 v_0 w_0 of the pending update
             d[k] = pend ? W[k * n + k] - 2.0 * zv * zw : W[k * n + k];
-            e[k] = trivial ? x0 : alpha;
+            e[k] = h.e;
             *tau = t;
         }
     }
@@ -910,7 +923,7 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
                                                            int spin, int* __restrict__ gave_up,
                                                            double* __restrict__ d, double* __restrict__ e) {
     constexpr int R = kTrRows, NW = kTrThreads / 64;
-    __shared__ double red[2][NW];     // wave sums of v.p and |x|^2
+    __shared__ double red[2][NW];     // wave sums of v.p and of |x|^2 past its first element
     __shared__ double sums[NW][R];    // wave sums of the rows' products
     __shared__ double rv[R], rw[R];   // v and w at the block's rows
     __shared__ double rnext[R];       // A[r][k+1] at the block's rows
@@ -1019,7 +1032,7 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
             const int c = tid + u * kTrThreads;
             w[u] -= K * v[u];
             x[u] = c > k && c < n ? x[u] - (vk * w[u] + wk * v[u]) : 0.0;
-            s += x[u] * x[u];
+            s += c == k + 1 ? 0.0 : x[u] * x[u];
             if (c == k + 1) at_k1 = x[u];
             if (own[u] >= 0) {
                 rv[own[u]] = v[u];
@@ -1029,19 +1042,16 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
         s = wave_sum63(s);
         if (lane == 63) red[1][wv] = s;
         __syncthreads();
-        double norm2 = 0.0;
+        double rest2 = 0.0;
 #pragma unroll
-        for (int i = 0; i < NW; i++) norm2 += red[1][i];
-        const double x0 = at_k1;
-        const double nrm = sqrt(norm2);
-        const double alpha = x0 > 0 ? -nrm : nrm;  // reflect x onto alpha e1
-        const double v0 = x0 - alpha;
-        const double vnorm2 = norm2 - x0 * x0 + v0 * v0;
-        const bool trivial = !(vnorm2 > 0.0) || (norm2 - x0 * x0) <= 0.0;
-        tau = trivial ? 0.0 : 2.0 / vnorm2;
+        for (int i = 0; i < NW; i++) rest2 += red[1][i];
+        const HhReflect h = hh_reflect(at_k1, rest2);
+        const bool trivial = h.trivial;
+        const double v0 = h.v0;
+        tau = h.tau;
         if (rlast == n - 1 && tid == 0) {
             d[k] = at_k[2] - 2.0 * vk * wk;
-            e[k] = trivial ? x0 : alpha;
+            e[k] = h.e;
         }
         double acc[R];
 #pragma unroll

@@ -123,3 +123,42 @@ def test_checks_of_several_threads():
                 assert rep[k] == out[0][0][k]
             assert np.allclose(rep["min_eig"][1], out[0][0]["min_eig"][1], atol=1e-11)
             assert np.allclose(rep["max_eig"][1], out[0][0]["max_eig"][1], rtol=1e-11)
+
+
+def weakly_coupled(n, eps, seed):
+    """Next neighbours coupled by 1, all others by eps: a row's other elements
+    are far below its first one, yet above the tolerance."""
+    rng = np.random.default_rng(seed)
+    E = rng.uniform(-1.0, 1.0, size=(n, n)) * eps
+    return 2.0 * np.eye(n) + np.diag(np.ones(n - 1), 1) + np.diag(np.ones(n - 1), -1) + 0.5 * (E + E.T)
+
+
+@pytest.mark.parametrize("spin", [DEFAULT, COLUMNS])
+@pytest.mark.parametrize("eps", [1e-7, 9e-9, 1e-9, 1e-10, 1e-11, 1e-12])
+@pytest.mark.parametrize("n", [3, 4, 9, 30, 70, 300])
+def test_weakly_coupled_rows(n, eps, spin):
+    """No element of a row may be dropped for being small beside the first
+    (their squares are below its square's rounding from 1e-8 on)."""
+    C = weakly_coupled(n, eps, n)
+    rep, _ = check(device(C), spin=spin)
+    assert_spectrum(rep, C)
+
+
+@pytest.mark.parametrize("spin", [DEFAULT, COLUMNS])
+def test_weak_coupling_decides_the_sign(spin):
+    C = np.array([[2.0, 1.0, 9e-9], [1.0, 2.0, 1.0], [9e-9, 1.0, 2.0]]) - (2.0 - np.sqrt(2.0) + 2e-9) * np.eye(3)
+    rep, _ = check(device(C), spin=spin)
+    assert np.linalg.eigvalsh(C)[0] > 2e-9
+    assert_spectrum(rep, C)
+    assert rep["n_neg_eig"][1] == 0 and rep["chol_ok"][1] == 1
+
+
+@pytest.mark.parametrize("spin", [DEFAULT, COLUMNS])
+@pytest.mark.parametrize("n", [2, 5, 40, 600])
+def test_infinities_are_reported(n, spin):
+    """An infinite entry (an overflowed product) leaves no finite extremes."""
+    for i, j in ((0, 0), (n - 1, n - 1), (0, n - 1), (n // 2, n // 2)):
+        C = dense(n, n, 0.0)
+        C[i, j] = C[j, i] = np.inf
+        rep, _ = check(device(C), spin=spin)
+        assert np.isnan(rep["min_eig"][1]) and np.isnan(rep["max_eig"][1]) and rep["n_neg_eig"][1] == -1, (i, j)
