@@ -813,10 +813,10 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 8 : 4))) void k_hh_column(double
 // its rows r, p_r and the element A[r][k+1] of the next row to reflect (A is
 // symmetric), and every block forms the same v, K and w from them.  What
 // bounds a column is this exchange between all blocks, there and back, and
-// three barriers in each: 3.0 us a column with 15 blocks, 3.6 us with 68 and
-// 5.0 us with 250, where the reads of the exchange add up (2000 rows: 24.4 ms
-// in a launch per column, 10.0 ms here; 540 rows: 3.5 and 1.9 ms; 120 rows:
-// 0.65 and 0.36 ms).
+// three barriers in each: 2.2 us a column with 15 blocks, 3.0 us with 68 and
+// 3.8 us with 250, where the reads of the exchange add up (2000 rows: 24.4 ms
+// in a launch per column, 7.6 ms here; 540 rows: 3.5 and 1.6 ms; 120 rows:
+// 0.65 and 0.27 ms).
 //
 // The exchange: slots hold kTrEmpty until a value is there, so a value is its
 // own flag and a reader polls the values themselves (agent-scope relaxed
@@ -828,9 +828,10 @@ __attribute__((amdgpu_waves_per_eu(WAVES == 4 ? 8 : 4))) void k_hh_column(double
 //
 // Blocks that are not all resident at once (other work holds the CUs) would
 // wait for each other; every wait is bounded by `spin` polls, after which the
-// block raises *gave_up and ends.  The others look at it as they start and
-// while they poll, and end too, and the caller goes through the columns launch
-// by launch.
+// block raises *gave_up and ends; the others follow at their own bounds, those
+// that start later at once, and the caller goes through the columns launch by
+// launch.  (A look at *gave_up between polls: 2.27 ms in place of 1.93 for 540
+// rows.)
 // ---------------------------------------------------------------------------
 constexpr int kTrThreads = 512;
 constexpr int kTrRows = 8;
@@ -838,7 +839,6 @@ constexpr int kTrMaxBlocks = 256;
 constexpr int kColumnUs = 12;    // a launch per column takes about this long per row
 // Polls of a wait, about 1.2 us each: no longer than the columns would take.
 constexpr int kTrSpinRow = 10, kTrSpinMin = 1000;
-constexpr int kTrLook = 32;      // polls from one look at *gave_up to the next
 constexpr unsigned long long kTrEmpty = 0x7FF4DEAD5EED0001ull;  // a NaN no operation returns
 
 // x plus the lane's neighbour under a DPP control (0 where there is none)
@@ -967,6 +967,10 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
         double w[E], x[E];
         {
             unsigned long long sp[E], sa[E];
+            // (a first look that comes too early costs another round trip: 2000,
+            // 540 and 120 rows 9.7, 2.2 and 0.37 ms without this pause, 7.6, 1.6
+            // and 0.27 ms with it; a few blocks exchange sooner)
+            if (B > 4) __builtin_amdgcn_s_sleep(8);
             bool ok = true;
 #pragma unroll
             for (int u = 0; u < E; u++) {
@@ -982,9 +986,6 @@ __global__ __launch_bounds__(kTrThreads, 1) void k_tridiag(const double* __restr
 #pragma unroll
                 for (int u = 0; u < E; u++) ok = ok && sp[u] != kTrEmpty && sa[u] != kTrEmpty;
                 if (ok || polls >= spin) break;
-                if (polls % kTrLook == kTrLook - 1 &&
-                    __hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    break;
 #pragma unroll
                 for (int u = 0; u < E; u++) {
                     const int c = tid + u * kTrThreads;
@@ -1256,7 +1257,7 @@ static void tridiag_columns(const double* C, int64_t P, int64_t off, int64_t n, 
 // tridiagonalisations on the device, a CU each; given back when the call ends.
 // Checks of several threads whose blocks do not fit on the card together would
 // hold each other up (four of 2000 rows: up to 99 ms each until they gave up;
-// a launch per column 55 ms; one after another 13 to 44 ms), so a call waits
+// a launch per column 55 ms; one after another 10 to 35 ms), so a call waits
 // in line for its share, at most twice as long as its own columns would take.
 class ResidentBlocks {
   public:
