@@ -1114,19 +1114,24 @@ __global__ void k_hh_tail(const double* __restrict__ W, int64_t n, HhPending q, 
     d[n - 1] = hh_apply(W[(n - 1) * n + n - 1], q, K, n >= 2 ? 1 : 0, n >= 2 ? 1 : 0);
 }
 
-// Eigenvalue counts of the tridiagonal (d, e).  The number of eigenvalues
-// below x is the number of sign changes in the sequence of leading principal
-// minors p_i = (d_i - x) p_{i-1} - e_{i-1}^2 p_{i-2} (Givens' Sturm sequence):
-// one fused multiply-add on the critical path of a step, where the quotients
-// p_i / p_{i-1} need a float64 division.  d and e are first scaled by a power
-// of two to a spectrum within [-4, 4]; every fourth step both minors are
-// scaled by a power of two, so they neither overflow nor underflow: a step
-// shrinks them by 2^-220 at most, since squares of off-diagonals below
-// kMinE2 are taken as kMinE2 (an error of 2^-110 of the spectrum).  A
-// diagonal equal to x counts as below it (kTie).
-constexpr double kMinE2 = 0x1p-220, kTie = 0x1p-100;
+// Eigenvalue counts of the tridiagonal (d, e), scaled by a power of two to a
+// spectrum within [-4, 4].  de: pairs (d_i, e_{i-1}^2), i < n, with e_{-1} = 0.
+//
+// sturm_count: the number of eigenvalues below x is the number of sign changes
+// in the sequence of leading principal minors p_i = (d_i - x) p_{i-1} -
+// e_{i-1}^2 p_{i-2} (Givens' Sturm sequence): one fused multiply-add on the
+// critical path of a step, where the quotients p_i / p_{i-1} need a float64
+// division.  Every fourth step both minors are scaled by a power of two, so
+// they neither overflow nor underflow: a step shrinks them by 2^-220 at most,
+// since squares of off-diagonals below kMinE2 are staged as kMinE2.  A diagonal
+// equal to x counts as below it (kTie).  The two move the eigenvalues by less
+// than kSturmError, an ulp of those beyond kSturmSmall.
+//
+// sturm_quotients: the same from the quotients, without those two: the sign of
+// an eigenvalue near zero, however graded the matrix (1 beside 1e-31).  A
+// quotient below DBL_MIN counts as negative.
+constexpr double kMinE2 = 0x1p-220, kTie = 0x1p-100, kSturmError = 0x1p-98, kSturmSmall = 0x1p-46;
 
-// de: pairs (d_i, e_{i-1}^2), i < n, with e_{-1} = 0, scaled.
 __device__ __forceinline__ int sturm_count(const double2* de, int64_t n, double x) {
     double p1 = 1.0, p2 = 0.0;  // p_{i-1}, p_{i-2}
     int c = 0;
@@ -1146,6 +1151,18 @@ __device__ __forceinline__ int sturm_count(const double2* de, int64_t n, double 
         p2 = __builtin_amdgcn_ldexp(p2, ex);
     }
     for (; i < n; i++) step(i);
+    return c;
+}
+
+__device__ __noinline__ int sturm_quotients(const double2* de, int64_t n, double x) {
+    double q = 1.0;
+    int c = 0;
+    for (int64_t i = 0; i < n; i++) {
+        const double2 v = de[i];
+        q = (v.x - x) - v.y / q;
+        if (fabs(q) < DBL_MIN) q = -DBL_MIN;
+        c += q < 0.0 ? 1 : 0;
+    }
     return c;
 }
 
@@ -1198,37 +1215,62 @@ __global__ __launch_bounds__(kBisectThreads) void k_bisect(const double* __restr
         return;
     }
     const int ex = -__builtin_amdgcn_frexp_exp(span);
-    auto scaled = [&](int64_t i) {
-        const double o = i > 0 ? __builtin_amdgcn_ldexp(e[i - 1], ex) : 0.0;
-        return make_double2(__builtin_amdgcn_ldexp(d[i], ex), i > 0 ? fmax(o * o, kMinE2) : 0.0);
-    };
     const bool staged = n <= kBisectLds;
     double2* de = staged ? de_l : de_g + int64_t(blockIdx.x) * n;
-    for (int64_t i = tid; i < n; i += kBisectThreads) de[i] = scaled(i);
-    __syncthreads();
+    auto stage = [&](double floor) {
+        for (int64_t i = tid; i < n; i += kBisectThreads) {
+            const double o = i > 0 ? __builtin_amdgcn_ldexp(e[i - 1], ex) : 0.0;
+            de[i] = make_double2(__builtin_amdgcn_ldexp(d[i], ex), i > 0 ? fmax(o * o, floor) : 0.0);
+        }
+        __syncthreads();
+    };
+    stage(blockIdx.x == 2 ? 0.0 : kMinE2);
     auto count = [&](double x) { return staged ? sturm_count(de_l, n, x) : sturm_count(de, n, x); };
     if (blockIdx.x == 2) {
-        if (tid == 0) out[2] = double(count(0.0));
+        if (tid == 0) out[2] = double(sturm_quotients(de, n, 0.0));
         return;
     }
     // block 0: smallest x with count(x) >= 1; block 1: smallest x with count(x) >= n
     lo = __builtin_amdgcn_ldexp(lo, ex) - 2.0 * DBL_EPSILON * n;
     hi = __builtin_amdgcn_ldexp(hi, ex) + 2.0 * DBL_EPSILON * n;
     const int target = blockIdx.x == 0 ? 1 : int(n);
-    for (int it = 0; it < 12; it++) {
-        const double x = lo + (hi - lo) * double(tid + 1) / double(kBisectThreads + 1);
-        // bracket: the first point with count >= target, and the one before it
-        const unsigned long long at = __builtin_amdgcn_ballot_w64(count(x) >= target);
+    // cuts [lo, hi] at the points of all threads, in increasing order; below(x):
+    // at least target eigenvalues lie below x
+    auto cut = [&](auto&& point, auto&& below) {
+        // bracket: the first point above the eigenvalue, and the one before it
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(below(point(tid)));
         if (lane == 0) first_s[wv] = at ? 64 * wv + __builtin_ctzll(at) : kBisectThreads;
         __syncthreads();
         int q = kBisectThreads;
         for (int w = 0; w < NW; w++) q = min(q, first_s[w]);
         __syncthreads();
-        const double nlo = q > 0 ? lo + (hi - lo) * double(q) / double(kBisectThreads + 1) : lo;
-        const double nhi = q < kBisectThreads ? lo + (hi - lo) * double(q + 1) / double(kBisectThreads + 1) : hi;
+        const double nlo = q > 0 ? fmax(lo, point(q - 1)) : lo;
+        const double nhi = q < kBisectThreads ? fmin(hi, point(q)) : hi;
         lo = nlo;
         hi = nhi;
-        if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi))) break;
+    };
+    auto even = [&](int t) { return lo + (hi - lo) * double(t + 1) / double(kBisectThreads + 1); };
+    auto size = [&] { return fmax(fabs(lo), fabs(hi)); };
+    auto done = [&] { return hi - lo <= 2.0 * DBL_EPSILON * size(); };
+    auto small = [&] { return size() < kSturmSmall && hi - lo < 0x1p8 * kSturmError; };
+    for (int it = 0; it < 14 && !done() && !small(); it++) cut(even, [&](double x) { return count(x) >= target; });
+    if (!done() && small()) {
+        // near zero, where the minors' error begins to show, the quotients take
+        // over; a bracket around zero is first cut at +-m 2^(-7 t), which
+        // leaves a sign and a few octaves
+        stage(0.0);
+        lo -= kSturmError;
+        hi += kSturmError;
+        auto below = [&](double x) { return sturm_quotients(de, n, x) >= target; };
+        if (lo < 0.0 && hi > 0.0) {
+            const double m = size();
+            cut([&](int t) {
+                return t < kBisectThreads / 2 ? -__builtin_amdgcn_ldexp(m, -7 * t)
+                                              : __builtin_amdgcn_ldexp(m, -7 * (kBisectThreads - 1 - t));
+            }, below);
+        }
+        if (lo < 0.0 && hi > 0.0) lo = hi = 0.0;  // within 2^-900 of it
+        for (int it = 0; it < 12 && !done(); it++) cut(even, below);
     }
     if (tid == 0) out[blockIdx.x] = __builtin_amdgcn_ldexp(0.5 * (lo + hi), -ex);
 }

@@ -162,3 +162,49 @@ def test_infinities_are_reported(n, spin):
         C[i, j] = C[j, i] = np.inf
         rep, _ = check(device(C), spin=spin)
         assert np.isnan(rep["min_eig"][1]) and np.isnan(rep["max_eig"][1]) and rep["n_neg_eig"][1] == -1, (i, j)
+
+
+@pytest.mark.parametrize("small", [1e-20, 1e-31, 1e-36, 1e-60, 1e-120, 1e-250])
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 1e60])
+def test_graded_blocks(small, scale):
+    """Eigenvalues far below the largest, uncoupled from it: their signs, and
+    the extreme one to its own precision."""
+    for d in ([1.0, small], [small, 1.0], [1.0, small, 2.0 * small, 1.0], [small] * 3 + [1.0] + [small] * 3):
+        rep, _ = check(device(np.diag(d) * scale))
+        assert rep["n_neg_eig"][1] == 0 and rep["chol_ok"][1] == 1
+        assert abs(rep["min_eig"][1] - small * scale) <= 1e-15 * small * scale
+        rep, _ = check(device(-np.diag(d) * scale))
+        assert rep["n_neg_eig"][1] == len(d) and rep["chol_ok"][1] == 0
+        assert abs(rep["max_eig"][1] + small * scale) <= 1e-15 * small * scale
+    d = np.diag([1.0, -small, small, 0.0]) * scale
+    rep, _ = check(device(d))
+    assert rep["n_neg_eig"][1] == 2  # a zero counts as below zero
+    assert abs(rep["min_eig"][1] + small * scale) <= 1e-15 * small * scale
+
+
+@pytest.mark.parametrize("n", [2, 9, 100, 700, 3100])
+def test_graded_dense_blocks(n):
+    """The same with a dense block 1e-33 of the other's size (3100 rows: counts
+    from global memory)."""
+    T = dense(n // 2, n, -0.1)
+    C = np.zeros((n, n))
+    C[: n - n // 2, : n - n // 2] = np.diag(np.linspace(1.0, 2.0, n - n // 2))
+    C[n - n // 2:, n - n // 2:] = 1e-33 * T
+    w = np.linalg.eigvalsh(T)
+    tol = 20 * n * 2.3e-16 * w[-1]
+    rep, _ = check(device(C))
+    assert rep["n_neg_eig"][1] == 0 and rep["chol_ok"][1] == 1
+    assert abs(rep["min_eig"][1] - 1e-33 * w[0]) <= 1e-33 * tol
+    rep, _ = check(device(-C))
+    assert rep["n_neg_eig"][1] == n and abs(rep["max_eig"][1] + 1e-33 * w[0]) <= 1e-33 * tol
+
+
+def test_zero_rows_in_a_block():
+    """Constant elements: zero eigenvalues among the others."""
+    C = dense(300, 5, 0.0)
+    z = [0, 7, 150, 299]
+    C[z, :] = 0.0
+    C[:, z] = 0.0
+    rep, _ = check(device(C))
+    assert rep["chol_ok"][1] == 0
+    assert_spectrum(rep, C)  # (the reflections carry rounding into the zeros)
