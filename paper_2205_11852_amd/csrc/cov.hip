@@ -451,22 +451,18 @@ __global__ void k_zero_flags(CheckFlags* fl, int n) {
 // panel is one launch of single waves: every block factors the 32 x 32
 // diagonal block for itself (row i in lane i's registers, the column's other
 // elements through readlane) and with the same broadcast elements solves 64
-// rows below it, one per lane: 17 us, where a launch for the diagonal block
+// rows below it, one per lane: 20 us, where a launch for the diagonal block
 // (one thread forming each pivot) took 46 us and one for the rows 52 us.  The
 // update is a contraction over the panel's 32 columns and runs on the matrix
-// cores: 13 us, 24 us before.  2000 rows: 8.0 ms before, 2.0 ms now.
+// cores: 13 us, 24 us before.  2000 rows: 8.0 ms before, 2.1 ms now.  Square
+// roots and quotients are the correctly rounded ones (the hardware's estimate of
+// 1 / sqrt and two Newton steps in their place: 17 us, errors of an ulp or two,
+// and a NaN from an infinite pivot).
 constexpr int kNB = 32;
 
 __device__ __forceinline__ double readlane_f64(double x, int l) {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
                             __builtin_amdgcn_readlane(__double2loint(x), l));
-}
-
-// 1 / sqrt(d) to about an ulp: the hardware's estimate, two Newton steps.
-__device__ __forceinline__ double rsqrt_f64(double d) {
-    double r = __builtin_amdgcn_rsq(d);
-    r = r * fma(-0.5 * d * r, r, 1.5);
-    return r * fma(-0.5 * d * r, r, 1.5);
 }
 
 // Columns [k0, k0 + nb) of L from the updated W: the rows below the diagonal
@@ -497,10 +493,10 @@ __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int6
     for (int j = 0; j < kNB; j++) {
         const double d = readlane_f64(r[j], j);
         bad |= !(d > 0.0);
-        const double inv = rsqrt_f64(d);
-        const double l = r[j] * inv;
+        const double s = sqrt(d);
+        const double l = r[j] / s;
         r[j] = l;
-        x[j] *= inv;
+        x[j] /= s;
 #pragma unroll
         for (int c = j + 1; c < kNB; c++) {
             const double lc = readlane_f64(l, c);
@@ -1172,8 +1168,8 @@ __device__ __noinline__ int sturm_quotients(const double2* de, int64_t n, double
 // round is bound by the serial recurrence of one count, a step of which
 // takes about 30 cycles), block 2 counts the eigenvalues below 0.  Up to
 // kBisectLds entries are read from LDS, more from the global scratch `de`
-// (3 n pairs).  2000 rows: 2.3 ms with quotients, 0.49 ms here; 540 rows: 0.77
-// and 0.15 ms.
+// (3 n pairs).  2000 rows: 2.3 ms with quotients, 0.6 ms here; 540 rows: 0.77
+// and 0.16 ms.
 constexpr int kBisectThreads = 256;
 constexpr int64_t kBisectLds = 3072;  // 48 KB of LDS for the pairs
 __global__ __launch_bounds__(kBisectThreads) void k_bisect(const double* __restrict__ d, const double* __restrict__ e,

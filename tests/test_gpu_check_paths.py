@@ -208,3 +208,30 @@ def test_zero_rows_in_a_block():
     rep, _ = check(device(C))
     assert rep["chol_ok"][1] == 0
     assert_spectrum(rep, C)  # (the reflections carry rounding into the zeros)
+
+
+@pytest.mark.parametrize("n", [2, 5, 31, 32, 33, 64, 70, 200])
+def test_cholesky_of_integer_factors(n):
+    """C = L L^T with whole numbers in L: correctly rounded square roots and
+    quotients make every step exact, so a last pivot of exactly zero is seen as
+    zero, and one of 1 beside entries of millions as 1."""
+    for seed in range(12):
+        rng = np.random.default_rng(1000 * n + seed)
+        L = np.tril(rng.integers(-60, 61, (n, n)).astype(float))
+        np.fill_diagonal(L, rng.integers(1, 1000, n))
+        for last, ok in ((0.0, 0), (1.0, 1)):
+            L[-1, -1] = last
+            rep, _ = check(device(L @ L.T))
+            assert rep["chol_ok"][1] == ok, (seed, last)
+
+
+@pytest.mark.parametrize("n", [2, 33, 70])
+def test_cholesky_infinite_pivots(n):
+    """An infinite diagonal entry is a positive pivot; its column is zero."""
+    for i in (0, n // 2, n - 1):
+        d = np.arange(1.0, n + 1.0)
+        d[i] = np.inf
+        rep, _ = check(device(np.diag(d)))
+        assert rep["chol_ok"][1] == 1
+        rep, _ = check(device(np.diag(-d)))
+        assert rep["chol_ok"][1] == 0
