@@ -1365,7 +1365,7 @@ static lc_status make_plan(DeviceCtx* ctx, const lc_cells* cells, const lc_task*
             // bins or the midpoint kernel's j tables: two of them fit where
             // one 16-wave block did)
             int best = -1;
-            for (int w : {getenv("LC_W1") ? 1 : 4, getenv("LC_W1") ? 2 : 4, 4, 8, 12, 16}) {
+            for (int w : {4, 8, 12, 16}) {
                 if (w == 12 && !h16 && !mid) continue;
                 if (lds_of(sh, w) > ctx->max_lds_block) continue;
                 int o = 0;
