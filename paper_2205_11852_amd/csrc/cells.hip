@@ -361,14 +361,12 @@ using namespace lc;
 
 static void free_cells_mem(lc_cells* c) {
     if (!c || (!c->pts && !c->cs)) return;
-    // any stream may have counted on the mesh: as hipFree would, wait for all
-    // of them before the buffers can be handed out again
+    // any stream may have counted on the mesh
     int cur = c->device;
     (void)hipGetDevice(&cur);
     if (cur != c->device) (void)hipSetDevice(c->device);
-    (void)hipDeviceSynchronize();
-    dev_free_idle(c->pts);
-    dev_free_idle(c->cs);
+    void* const bufs[2] = {c->pts, c->cs};
+    dev_free_unused(bufs, 2);
     if (cur != c->device) (void)hipSetDevice(cur);
     c->pts = nullptr;
     c->cs = nullptr;

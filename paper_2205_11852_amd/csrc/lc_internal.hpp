@@ -67,6 +67,7 @@ struct ScratchBlock {
     hipStream_t s = nullptr;
     bool idle = true;
 };
+using ScratchList = std::list<ScratchBlock>;
 
 class ResidentBlocks;
 
@@ -82,10 +83,12 @@ struct DeviceCtx {
     int resident_blocks = 0;            // blocks of the resident tridiagonalisations under way
     std::list<const ResidentBlocks*> resident_line;  // calls that wait to start theirs
     std::mutex scratch_mu;              // guards the scratch cache
-    std::list<ScratchBlock> scratch;    // freed buffers, oldest first
+    ScratchList scratch;                // freed buffers, oldest first
     size_t scratch_bytes = 0;           // their sum
     size_t scratch_cap = 0;             // and its bound
-    std::unordered_map<void*, ScratchBlock> scratch_live;
+    ScratchList scratch_wait;           // freed, but some stream may still use them
+    ScratchList scratch_out;            // handed out
+    std::unordered_map<void*, ScratchList::iterator> scratch_live;  // by address
 };
 
 // Context of the current device (created on first use).
@@ -107,11 +110,12 @@ class Stager {
 };
 
 // Stream-ordered device memory from the device's scratch cache: dev_free
-// hands the buffer back as of this point of stream s, dev_alloc takes one
-// that is ready for stream s.  dev_free_idle: no queued work uses the buffer.
+// hands the buffer back as of this point of stream s, without waiting, and
+// dev_alloc takes one that is ready for stream s.  dev_free_unused: n buffers
+// (NULL allowed) that any stream may have used; waits for the device.
 lc_status dev_alloc(void** p, size_t bytes, hipStream_t s);
 void dev_free(void* p, hipStream_t s);
-void dev_free_idle(void* p);
+void dev_free_unused(void* const* ps, int n);
 
 // A stream-ordered device buffer that is freed on its stream when it goes
 // out of scope (or at reset()), so every early return releases what was

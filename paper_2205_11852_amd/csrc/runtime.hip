@@ -1,6 +1,8 @@
 // Error reporting, device contexts, pinned staging and stream-ordered scratch.
 #include <cstring>
+#include <iterator>
 #include <map>
+#include <new>
 
 #include "lc_internal.hpp"
 
@@ -47,12 +49,6 @@ lc_status get_ctx(DeviceCtx** out) {
     LC_TRY_HIP(hipGetDeviceProperties(&prop, dev));
     c->n_cu = prop.multiProcessorCount;
     c->max_lds_block = prop.sharedMemPerBlock;
-    // keep freed stream-ordered memory in the pool between calls
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-        uint64_t thr = UINT64_MAX;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-    }
     c->scratch_cap = prop.totalGlobalMem / 16;
     for (PinnedSlot& sl : c->pinned) LC_TRY_HIP(hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming));
     g_ctx[dev] = c;
@@ -112,12 +108,14 @@ lc_status Stager::commit(hipStream_t s, void** dev_base) {
 // rest of a small count call, and hipMalloc and hipFree of a mesh (100
 // catalogues of 1e5 points) more than building it; a buffer kept here costs
 // an event record.  Mesh, counts, xi, map and checked covariance of 32 mocks
-// of 5000 points: 1220 -> 947 us; that mesh and one count on it 6.9 -> 1.5 ms.  A buffer is handed
-// out for its size class only (at most an eighth larger than asked for), on
-// the stream it was freed on or, once its event has passed, on any.  What is
-// kept is bounded by a sixteenth of the device's memory (the oldest buffers
-// leave first), given up when an allocation fails and released by
-// lc_release_caches.  A capturing stream takes its memory from the graph.
+// of 5000 points: 1220 -> 947 us; that mesh and one count on it 6.9 -> 1.5 ms.
+// A buffer is handed out for its size class only (at most an eighth larger than
+// asked for), on the stream it was freed on or, once its event has passed, on
+// any.  What is kept is bounded by a sixteenth of the device's memory: beyond
+// it the oldest buffers whose work is done go back to the device, at every call
+// until it is met (no call waits for them).  An allocation that fails takes
+// what is kept, as does lc_release_caches.  A capturing stream takes its memory
+// from the graph.
 static size_t size_class(size_t n) {
     size_t step = 256;
     while (step * 8 < n) step <<= 1;
@@ -133,17 +131,83 @@ static bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// Gives a cached buffer's memory back to the device (scratch_mu held).
-static void scratch_drop(DeviceCtx* c, std::list<ScratchBlock>::iterator it) {
-    if (!it->idle) (void)hipEventSynchronize(it->ev);
-    if (it->ev) (void)hipEventDestroy(it->ev);
-    (void)hipFreeAsync(it->p, nullptr);
-    c->scratch_bytes -= it->size;
-    c->scratch.erase(it);
+// Waits until every stream of the device is idle.
+static bool device_wait() {
+    if (hipDeviceSynchronize() == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
 }
 
-static void scratch_drop_all(DeviceCtx* c) {
-    while (!c->scratch.empty()) scratch_drop(c, c->scratch.begin());
+static bool passed(const ScratchBlock& b) {
+    if (b.idle) return true;
+    if (hipEventQuery(b.ev) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Whether stream s may use the block (the wait also covers a stream handle that
+// was destroyed and given out again).
+static bool ready(const ScratchBlock& b, hipStream_t s) {
+    if (b.idle || b.s != s) return passed(b);
+    if (hipStreamWaitEvent(s, b.ev, 0) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Takes the oldest blocks beyond the bound that are done out of the cache
+// (scratch_mu held).
+static void over_cap(DeviceCtx* c, ScratchList& gone) {
+    for (auto it = c->scratch.begin(); it != c->scratch.end() && c->scratch_bytes > c->scratch_cap;) {
+        const auto next = std::next(it);
+        if (passed(*it)) {
+            c->scratch_bytes -= it->size;
+            gone.splice(gone.end(), c->scratch, it);
+        }
+        it = next;
+    }
+}
+
+// Returns blocks that are done to the device: at once, and without waiting for
+// anything (hipFreeAsync leaves them in the pool until some later
+// synchronisation).
+static void give_back(DeviceCtx* c, ScratchList& gone) {
+    if (gone.empty()) return;
+    for (ScratchBlock& b : gone) {
+        if (b.ev) (void)hipEventDestroy(b.ev);
+        (void)hipFree(b.p);
+    }
+    gone.clear();
+    hipMemPool_t pool;
+    if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+}
+
+// Everything cached, back to the device (where HIP refuses the wait, what is
+// not done stays).
+static void drop_scratch(DeviceCtx* c) {
+    ScratchList gone;
+    {
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        gone.splice(gone.end(), c->scratch);
+        c->scratch_bytes = 0;
+    }
+    if (!device_wait()) {
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        for (auto it = gone.begin(); it != gone.end();) {
+            const auto next = std::next(it);
+            if (!passed(*it)) {
+                c->scratch_bytes += it->size;
+                c->scratch.splice(c->scratch.end(), gone, it);
+            }
+            it = next;
+        }
+    }
+    give_back(c, gone);
+}
+
+static lc_status alloc_failed(size_t bytes, hipError_t e) {
+    (void)hipGetLastError();
+    return fail(e == hipErrorOutOfMemory ? LC_ERR_NOMEM : LC_ERR_HIP, "device allocation of %zu bytes failed: %s",
+                bytes, hipGetErrorString(e));
 }
 
 lc_status dev_alloc(void** p, size_t bytes, hipStream_t s) {
@@ -152,76 +216,117 @@ lc_status dev_alloc(void** p, size_t bytes, hipStream_t s) {
     DeviceCtx* c;
     LC_TRY(get_ctx(&c));
     const bool cap = capturing(s);
-    std::lock_guard<std::mutex> lk(c->scratch_mu);
-    if (!cap) {
-        for (auto it = c->scratch.begin(); it != c->scratch.end(); ++it) {
-            if (it->size != n) continue;
-            if (!it->idle) {
-                // (the wait also covers a stream handle that was destroyed
-                // and given out again)
-                const hipError_t e = it->s == s ? hipStreamWaitEvent(s, it->ev, 0) : hipEventQuery(it->ev);
-                if (e != hipSuccess) {
-                    (void)hipGetLastError();
-                    continue;
-                }
-            }
-            *p = it->p;
-            c->scratch_bytes -= n;
-            c->scratch_live.emplace(it->p, *it);
-            c->scratch.erase(it);
-            return LC_OK;
-        }
-    }
-    hipError_t e = hipMallocAsync(p, n, s);
-    if (e == hipErrorOutOfMemory && !cap && !c->scratch.empty()) {
-        (void)hipGetLastError();
-        scratch_drop_all(c);
-        (void)hipDeviceSynchronize();
-        e = hipMallocAsync(p, n, s);
-    }
-    if (e != hipSuccess) {
+    if (cap) {
+        const hipError_t e = hipMallocAsync(p, n, s);
+        if (e == hipSuccess) return LC_OK;
         *p = nullptr;
-        (void)hipGetLastError();
-        return fail(e == hipErrorOutOfMemory ? LC_ERR_NOMEM : LC_ERR_HIP,
-                    "device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+        return alloc_failed(bytes, e);
     }
-    if (!cap) {
-        ScratchBlock b;
-        b.p = *p;
-        b.size = n;
-        c->scratch_live.emplace(b.p, b);
+    try {
+        ScratchList node, gone;
+        {
+            std::lock_guard<std::mutex> lk(c->scratch_mu);
+            for (auto it = c->scratch.begin(); it != c->scratch.end(); ++it) {
+                if (it->size != n || !ready(*it, s)) continue;
+                c->scratch_live.emplace(it->p, it);
+                c->scratch_bytes -= n;
+                c->scratch_out.splice(c->scratch_out.end(), c->scratch, it);
+                *p = it->p;
+                break;
+            }
+            over_cap(c, gone);
+        }
+        give_back(c, gone);
+        if (*p) return LC_OK;
+        node.emplace_back();
+        node.front().size = n;
+        void* d = nullptr;
+        hipError_t e = hipMallocAsync(&d, n, s);
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            drop_scratch(c);
+            e = hipMallocAsync(&d, n, s);
+        }
+        if (e != hipSuccess) return alloc_failed(bytes, e);
+        node.front().p = d;
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        try {
+            c->scratch_live.emplace(d, node.begin());
+        } catch (...) {
+            (void)hipFreeAsync(d, s);
+            throw;
+        }
+        c->scratch_out.splice(c->scratch_out.end(), node);
+        *p = d;
+        return LC_OK;
+    } catch (const std::bad_alloc&) {
+        return fail(LC_ERR_NOMEM, "out of host memory in a device allocation of %zu bytes", bytes);
     }
-    return LC_OK;
 }
 
-static void scratch_put(void* p, hipStream_t s, bool idle) {
+void dev_free(void* p, hipStream_t s) {
     DeviceCtx* c;
     if (!p || get_ctx(&c) != LC_OK) return;
-    const bool cap = !idle && capturing(s);
-    std::lock_guard<std::mutex> lk(c->scratch_mu);
-    auto it = c->scratch_live.find(p);
-    if (it == c->scratch_live.end()) {
-        (void)hipFreeAsync(p, s);
-        return;
+    const bool cap = capturing(s);
+    ScratchList gone;
+    {
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        auto it = c->scratch_live.find(p);
+        if (it == c->scratch_live.end()) {
+            (void)hipFreeAsync(p, s);
+            return;
+        }
+        auto b = it->second;
+        c->scratch_live.erase(it);
+        b->s = s;
+        b->idle = false;
+        if (!b->ev && hipEventCreateWithFlags(&b->ev, hipEventDisableTiming) != hipSuccess) b->ev = nullptr;
+        if (cap || !b->ev || hipEventRecord(b->ev, s) != hipSuccess) {
+            (void)hipGetLastError();
+            if (b->ev) (void)hipEventDestroy(b->ev);
+            c->scratch_out.erase(b);
+            (void)hipFreeAsync(p, s);
+            return;
+        }
+        c->scratch.splice(c->scratch.end(), c->scratch_out, b);
+        c->scratch_bytes += b->size;
+        over_cap(c, gone);
     }
-    ScratchBlock b = it->second;
-    c->scratch_live.erase(it);
-    b.s = s;
-    b.idle = idle;
-    if (!idle && !b.ev && hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) b.ev = nullptr;
-    if (cap || (!idle && (!b.ev || hipEventRecord(b.ev, s) != hipSuccess))) {
-        (void)hipGetLastError();
-        if (b.ev) (void)hipEventDestroy(b.ev);
-        (void)hipFreeAsync(p, s);
-        return;
-    }
-    c->scratch.push_back(b);
-    c->scratch_bytes += b.size;
-    while (c->scratch_bytes > c->scratch_cap) scratch_drop(c, c->scratch.begin());
+    give_back(c, gone);
 }
 
-void dev_free(void* p, hipStream_t s) { scratch_put(p, s, false); }
-void dev_free_idle(void* p) { scratch_put(p, nullptr, true); }
+void dev_free_unused(void* const* ps, int n) {
+    DeviceCtx* c;
+    if (get_ctx(&c) != LC_OK) return;
+    ScratchList gone;
+    {
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        for (int i = 0; i < n; i++) {
+            auto it = ps[i] ? c->scratch_live.find(ps[i]) : c->scratch_live.end();
+            if (it == c->scratch_live.end()) continue;
+            c->scratch_wait.splice(c->scratch_wait.end(), c->scratch_out, it->second);
+            c->scratch_live.erase(it);
+        }
+        gone.splice(gone.end(), c->scratch_wait);
+    }
+    // any stream may have used them: they count as free after a wait for the
+    // whole device, this one or, where HIP refuses it, a later one
+    const bool idle = device_wait();
+    {
+        std::lock_guard<std::mutex> lk(c->scratch_mu);
+        if (!idle) {
+            c->scratch_wait.splice(c->scratch_wait.end(), gone);
+            return;
+        }
+        for (ScratchBlock& b : gone) {
+            b.idle = true;
+            c->scratch_bytes += b.size;
+        }
+        c->scratch.splice(c->scratch.end(), gone);
+        over_cap(c, gone);
+    }
+    give_back(c, gone);
+}
 
 }  // namespace lc
 
@@ -242,13 +347,8 @@ extern "C" void lc_release_caches(void) {
             sl.size = 0;
         }
     }
-    {
-        std::lock_guard<std::mutex> lk(c->scratch_mu);
-        lc::scratch_drop_all(c);
-    }
+    lc::dev_free_unused(nullptr, 0);
+    lc::drop_scratch(c);
     hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) {
-        (void)hipDeviceSynchronize();
-        (void)hipMemPoolTrimTo(pool, 0);
-    }
+    if (hipDeviceGetDefaultMemPool(&pool, c->device) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
 }

@@ -1,0 +1,181 @@
+"""The cache behind the library's scratch buffers and meshes (GPU): what it
+keeps is bounded and given back, calls on several streams do not share a buffer,
+asynchronous calls stay asynchronous, and stream captures go on."""
+import dataclasses
+import threading
+import time
+
+import numpy as np
+import pytest
+
+import mockgen
+
+pytestmark = pytest.mark.gpu
+
+GB = 1e9
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+
+    from paper_2205_11852_amd import lc
+
+    lc.lib()
+    return torch, lc
+
+
+@pytest.fixture(scope="module")
+def counting(env):
+    """A batch whose count holds the card for some 80 ms."""
+    torch, _ = env
+    from paper_2205_11852_amd.pipeline import Pipeline
+
+    wl = dataclasses.replace(mockgen.WORKLOADS["c2"], cfg_id=78, n_mock=64, n_subsets=50)
+    pl = Pipeline(mockgen.make_catalogues(wl))
+    pl.build_cells()
+    pl.count()
+    torch.cuda.synchronize()
+    return pl
+
+
+def _free(torch):
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _bound(torch):
+    return torch.cuda.mem_get_info()[1] / 16
+
+
+def _big_mesh(torch, lc, xyz, n_cat):
+    off = np.arange(n_cat + 1, dtype=np.int64) * (xyz.shape[1] // n_cat)
+    b = lc.Binning([0, 1 << 14, 1 << 15], 4, True, 1 << 22, lc.LC_LOS_Z)
+    return lc.lc_build_cells(xyz, off, b)
+
+
+def _points(torch, n):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    return torch.randint(0, 1 << 22, (3, n), generator=g, dtype=torch.int32, device="cuda")
+
+
+def test_freed_meshes_are_given_back(env):
+    """13 meshes of 2 GB at once: freeing them leaves at most the bound with
+    the library, lc_release_caches nothing."""
+    torch, lc = env
+    xyz = _points(torch, 160_000_000)
+    _big_mesh(torch, lc, xyz, 20).close()   # (the library's fixed buffers, the kernels' code)
+    lc.lc_release_caches()
+    before = _free(torch)
+    meshes = [_big_mesh(torch, lc, xyz, 20) for _ in range(13)]
+    held = before - _free(torch)
+    assert held > 13 * 2.0 * GB > 1.3 * _bound(torch)
+    for m in meshes:
+        m.close()
+    assert before - torch.cuda.mem_get_info()[0] <= _bound(torch) + 0.1 * GB
+    lc.lc_release_caches()
+    assert before - _free(torch) <= 0.1 * GB
+
+
+def _large_scratch(torch, lc, P, C, xi, stream=None):
+    """Sample covariances and A, B of two mocks: 5 P^2 float64 of scratch."""
+    lc.lc_covariance_general(xi, 2, P, 0, 1.0, 2.0, 50.0, lc.LC_FP64, None, None, C, report=False, stream=stream)
+
+
+def test_scratch_beyond_the_bound(env, counting):
+    """A buffer larger than all that may be kept is given back, and freeing it
+    does not wait for the kernels queued before."""
+    torch, lc = env
+    P = 28672
+    assert 24 * P * P > _bound(torch)
+    xi = torch.randn(2, 3, P, dtype=torch.float64, device="cuda")
+    C = torch.empty((P, P), dtype=torch.float64, device="cuda")
+    _large_scratch(torch, lc, P, C, xi)
+    lc.lc_release_caches()
+    before = _free(torch)
+    ev = torch.cuda.Event()
+    for _ in range(4):
+        counting.count()
+    ev.record()
+    t0 = time.perf_counter()
+    _large_scratch(torch, lc, P, C, xi)
+    queued = time.perf_counter() - t0
+    assert not ev.query(), "the call waited for the counts before it (%.0f ms)" % (1e3 * queued)
+    torch.cuda.synchronize()
+    i = torch.arange(0, P, 977, device="cuda")
+    got = C[i][:, i]
+    lc.lc_sample_covariance(xi, 2, P // 1000, lc.LC_FP64, C)   # the next call finds it done
+    assert before - _free(torch) <= _bound(torch) + 0.1 * GB
+    lc.lc_release_caches()
+    assert before - _free(torch) <= 0.1 * GB
+    x = xi[:, 2] - xi[:, 2].mean(0)
+    y = xi[:, :2] - xi[:, :2].mean(0)
+    cb = x[:, i].t() @ x[:, i]
+    ca = 0.5 * (y[:, 0, i].t() @ y[:, 0, i] + y[:, 1, i].t() @ y[:, 1, i])
+    ref = 2 * cb - ca + 2 * (ca - cb) / 50.0
+    assert torch.allclose(got, ref, rtol=1e-12, atol=1e-12)
+
+
+def test_allocation_after_the_cache_is_given_up(env):
+    """What an allocation lacks the cache gives up (other sizes are cached than
+    are asked for)."""
+    torch, lc = env
+    lc.lc_release_caches()
+    C = torch.empty(20000 * 20000, dtype=torch.float64, device="cuda")
+    xi = torch.randn(2, 3, 20000, dtype=torch.float64, device="cuda")
+
+    def call(P):
+        _large_scratch(torch, lc, P, C[:P * P], xi[:, :, :P].contiguous())
+        torch.cuda.synchronize()
+
+    call(16384)                                   # keeps 6 + 2 + 2 GiB
+    hold = torch.empty(int(_free(torch) - 3 * GB), dtype=torch.uint8, device="cuda")
+    call(14000)                                   # asks for 5 + 1.5 + 1.5 GiB
+    # more than there is, whatever is given up: refused, and the next call works
+    with pytest.raises(lc.LcError) as e:
+        call(20000)                               # 10 + 3.5 + 3.5 GiB
+    assert e.value.status == lc.LC_ERR_NOMEM
+    call(16384)
+    del hold
+    lc.lc_release_caches()
+
+
+def test_streams_do_not_share_buffers(env):
+    """Calls of the same sizes on three streams and threads, none waited for:
+    every result is its own input's."""
+    torch, lc = env
+    P, N, n = 300, 900, 24
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    x = torch.randn(3, n, N, P, generator=g, dtype=torch.float64, device="cuda")
+    ref = torch.empty((3, n, P, P), dtype=torch.float64, device="cuda")
+    out = torch.full_like(ref, float("nan"))
+    for t in range(3):
+        for i in range(n):
+            lc.lc_sample_covariance(x[t, i], N, P, lc.LC_FP64, ref[t, i])
+            torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    bar = threading.Barrier(3)
+
+    def work(t):
+        torch.cuda.set_device(0)
+        bar.wait()
+        for i in range(n):
+            lc.lc_sample_covariance(x[t, i], N, P, lc.LC_FP64, out[t, i], stream=streams[t])
+
+    for reps in range(3):
+        threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+        for th in threads:
+            th.start()
+        for th in threads:
+            th.join()
+        # and from one thread, in turn
+        for i in range(n):
+            for t in range(3):
+                lc.lc_sample_covariance(x[t, i], N, P, lc.LC_FP64, out[t, i], stream=streams[t])
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
