@@ -179,3 +179,75 @@ def test_streams_do_not_share_buffers(env):
         assert torch.equal(out, ref)
         out.fill_(float("nan"))
         torch.cuda.synchronize()
+
+
+# -- while a stream is being captured ---------------------------------------
+
+MODES = ["global", "thread_local", "relaxed"]
+
+
+def _captured(torch, mode, body):
+    """Runs body while another stream captures an addition; the graph must be
+    whole and add at every replay."""
+    y = torch.zeros(1000, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        g.capture_begin(capture_error_mode=mode)
+        y.add_(1.0)
+        body()
+        y.add_(1.0)
+        g.capture_end()
+    torch.cuda.synchronize()
+    for i in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, torch.full_like(y, 2.0 * (i + 1)))
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_scratch_while_a_stream_captures(env, counting, mode):
+    """Buffers that another stream still uses are looked at and left alone."""
+    torch, lc = env
+    P, N = 300, 900
+    x = torch.randn(N, P, dtype=torch.float64, device="cuda")
+    ref, a, b = (torch.empty((P, P), dtype=torch.float64, device="cuda") for _ in range(3))
+    lc.lc_release_caches()
+    lc.lc_sample_covariance(x, N, P, lc.LC_FP64, ref)
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(one):
+        counting.count()
+    lc.lc_sample_covariance(x, N, P, lc.LC_FP64, a, stream=one)   # its buffers are free after the count
+
+    _captured(torch, mode, lambda: lc.lc_sample_covariance(x, N, P, lc.LC_FP64, b, stream=two))
+    assert torch.equal(a, ref) and torch.equal(b, ref)
+
+
+@pytest.mark.parametrize("other_thread", [False, True])
+@pytest.mark.parametrize("mode", MODES)
+def test_mesh_freed_while_a_stream_captures(env, counting, mode, other_thread):
+    """A mesh that the garbage collector may free at any time: the capture goes
+    on, and the mesh's buffers are not handed out while a count reads them."""
+    torch, lc = env
+    pl = counting
+    want = pl.counts.clone()
+    pl.build_cells()
+    one = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(one):
+        pl.counts.zero_()
+        pl.count()
+
+    def body():
+        if not other_thread:
+            return pl.cells.close()
+        t = threading.Thread(target=pl.cells.close)
+        t.start()
+        t.join()
+
+    _captured(torch, mode, body)
+    pl.build_cells()     # takes the freed buffers
+    torch.cuda.synchronize()
+    assert torch.equal(pl.counts, want)
