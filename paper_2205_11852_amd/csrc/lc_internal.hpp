@@ -48,8 +48,8 @@ lc_status fail(lc_status code, const char* fmt, ...);
 // ---------------------------------------------------------------------------
 // per-device context
 // ---------------------------------------------------------------------------
-// One pinned block of a small ring for host->device parameter copies; its
-// event tells when the copy out of it is done.
+// A pinned block for host->device parameter copies (one of a small ring, or
+// the one for large copies); its event tells when the copy out of it is done.
 struct PinnedSlot {
     void* p = nullptr;
     size_t size = 0;
@@ -57,6 +57,7 @@ struct PinnedSlot {
     bool pending = false;
 };
 constexpr int kPinnedSlots = 8;
+constexpr size_t kPinnedSlot = 256 << 10;
 
 // A device buffer of the scratch cache: on stream s up to event ev (recorded
 // when it was freed; `idle`: no work uses it, ev says nothing).
@@ -75,9 +76,10 @@ struct DeviceCtx {
     int device = -1;
     int n_cu = 0;
     size_t max_lds_block = 65536;
-    std::mutex mu;                      // guards the pinned ring
+    std::mutex mu;                      // guards the pinned blocks
     PinnedSlot pinned[kPinnedSlots];
     int pinned_next = 0;
+    PinnedSlot pinned_large;
     std::mutex resident_mu;             // guards the next three
     std::condition_variable resident_cv;
     int resident_blocks = 0;            // blocks of the resident tridiagonalisations under way

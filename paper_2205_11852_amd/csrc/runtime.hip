@@ -51,6 +51,7 @@ lc_status get_ctx(DeviceCtx** out) {
     c->max_lds_block = prop.sharedMemPerBlock;
     c->scratch_cap = prop.totalGlobalMem / 16;
     for (PinnedSlot& sl : c->pinned) LC_TRY_HIP(hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming));
+    LC_TRY_HIP(hipEventCreateWithFlags(&c->pinned_large.ev, hipEventDisableTiming));
     g_ctx[dev] = c;
     *out = c;
     return LC_OK;
@@ -63,32 +64,68 @@ size_t Stager::push(const void* src, size_t bytes) {
     return off;
 }
 
+// Calls that HIP refuses, breaking the capture, while this thread (or in
+// global mode any thread) captures a stream: queries and waits of events,
+// synchronous allocation.  They touch no capturing stream here.
+class RelaxedCapture {
+  public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
 // The host bytes go through a ring of pinned blocks, so that a call does not
 // wait for the copy of the call before it, which the stream makes only after
 // the kernels queued before that call (with the scratch cache below,
 // back-to-back counts of 5 tasks of 3001 points went from 86 to 79 us a call).
-lc_status Stager::commit(hipStream_t s, void** dev_base) {
-    const size_t n = host_.size() ? host_.size() : 1;
-    std::lock_guard<std::mutex> lk(ctx_->mu);
-    PinnedSlot& sl = ctx_->pinned[ctx_->pinned_next];
-    ctx_->pinned_next = (ctx_->pinned_next + 1) % kPinnedSlots;
+// The ring is one allocation, made once; what is larger than its slots goes
+// through a block of its own, which grows with the largest.
+static lc_status pinned_room(DeviceCtx* c, PinnedSlot& sl, size_t n) {
+    RelaxedCapture relaxed;
     if (sl.pending) {
         // the last copy out of this block must have finished
         LC_TRY_HIP(hipEventSynchronize(sl.ev));
         sl.pending = false;
     }
-    if (sl.size < n) {
+    if (&sl == &c->pinned_large) {
+        if (sl.size >= n) return LC_OK;
         if (sl.p) LC_TRY_HIP(hipHostFree(sl.p));
         sl.p = nullptr;
         sl.size = 0;
-        size_t sz = 1 << 14;
+        size_t sz = 2 * kPinnedSlot;
         while (sz < n) sz <<= 1;
         if (hipHostMalloc(&sl.p, sz, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
             sl.p = nullptr;
             return fail(LC_ERR_NOMEM, "pinned staging allocation of %zu bytes failed", sz);
         }
         sl.size = sz;
+    } else if (!sl.p) {
+        void* ring = nullptr;
+        if (hipHostMalloc(&ring, kPinnedSlots * kPinnedSlot, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(LC_ERR_NOMEM, "pinned staging allocation of %zu bytes failed", kPinnedSlots * kPinnedSlot);
+        }
+        for (int i = 0; i < kPinnedSlots; i++) {
+            c->pinned[i].p = static_cast<unsigned char*>(ring) + i * kPinnedSlot;
+            c->pinned[i].size = kPinnedSlot;
+        }
     }
+    return LC_OK;
+}
+
+lc_status Stager::commit(hipStream_t s, void** dev_base) {
+    const size_t n = host_.size() ? host_.size() : 1;
+    std::lock_guard<std::mutex> lk(ctx_->mu);
+    PinnedSlot* slot = &ctx_->pinned_large;
+    if (n <= kPinnedSlot) {
+        slot = &ctx_->pinned[ctx_->pinned_next];
+        ctx_->pinned_next = (ctx_->pinned_next + 1) % kPinnedSlots;
+    }
+    PinnedSlot& sl = *slot;
+    LC_TRY(pinned_room(ctx_, sl, n));
     if (!host_.empty()) std::memcpy(sl.p, host_.data(), host_.size());
     void* d = nullptr;
     LC_TRY(dev_alloc(&d, n, s));
@@ -130,18 +167,6 @@ static bool capturing(hipStream_t s) {
     }
     return st != hipStreamCaptureStatusNone;
 }
-
-// Calls that HIP refuses, breaking the capture, while this thread (or in
-// global mode any thread) captures a stream: queries of events and
-// synchronous allocation.  They touch no capturing stream here.
-class RelaxedCapture {
-  public:
-    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
-    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
-
-  private:
-    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
-};
 
 // Waits until every stream of the device is idle: what hipFree does first.
 // (hipDeviceSynchronize would break the captures of all threads.)
@@ -358,13 +383,18 @@ extern "C" void lc_release_caches(void) {
     lc::release_tuning();
     {
         std::lock_guard<std::mutex> lk(c->mu);
-        for (lc::PinnedSlot& sl : c->pinned) {
+        lc::RelaxedCapture relaxed;
+        auto done = [](lc::PinnedSlot& sl) {
             if (sl.pending) (void)hipEventSynchronize(sl.ev);
             sl.pending = false;
-            if (sl.p) (void)hipHostFree(sl.p);
-            sl.p = nullptr;
-            sl.size = 0;
-        }
+        };
+        for (lc::PinnedSlot& sl : c->pinned) done(sl);
+        done(c->pinned_large);
+        if (c->pinned[0].p) (void)hipHostFree(c->pinned[0].p);  // (the whole ring)
+        if (c->pinned_large.p) (void)hipHostFree(c->pinned_large.p);
+        for (lc::PinnedSlot& sl : c->pinned) sl.p = nullptr;
+        c->pinned_large.p = nullptr;
+        c->pinned_large.size = 0;
     }
     lc::dev_free_unused(nullptr, 0);
     lc::drop_scratch(c);
