@@ -59,8 +59,9 @@ __device__ __forceinline__ void xi_multipoles(const double* xs, const double* ws
 
 __global__ __launch_bounds__(kXiThreads) void k_xi(const unsigned long long* __restrict__ counts,
                                                    const int32_t* __restrict__ est, const double* __restrict__ norm,
-                                                   const double* __restrict__ W, int32_t n_mock,
-                                                   int32_t n_r, int32_t n_mu, int32_t rows_max, int32_t groups, double* __restrict__ xi) {
+                                                   const double* __restrict__ W, int32_t n_mock, int32_t n_r,
+                                                   int32_t n_mu, int32_t rows_max, int32_t groups,
+                                                   double* __restrict__ xi) {
 #pragma clang fp contract(off)
     for (int64_t blk = blockIdx.x; blk < int64_t(n_mock) * groups; blk += gridDim.x) {
         const int64_t mk = blk / groups;
@@ -98,10 +99,10 @@ __global__ __launch_bounds__(kXiThreads) void k_xi(const unsigned long long* __r
                 out[q * P + o] = x[q];
                 xs[q * nbin + t] = x[q];
             }
-    }
-    __syncthreads();
-    xi_multipoles<3>(xs, ws, rows, k0, n_r, n_mu, P, out);
-    __syncthreads();
+        }
+        __syncthreads();
+        xi_multipoles<3>(xs, ws, rows, k0, n_r, n_mu, P, out);
+        __syncthreads();
     }
 }
 
@@ -113,9 +114,9 @@ __global__ __launch_bounds__(kXiThreads) void k_xi(const unsigned long long* __r
 __global__ __launch_bounds__(kXiThreads) void k_xi_split(const unsigned long long* __restrict__ counts,
                                                          const int32_t* __restrict__ est,
                                                          const double* __restrict__ norm,
-                                                         const double* __restrict__ W, int32_t n_mock,
-                                                         int32_t n_sub, int32_t n_r, int32_t n_mu, int32_t rows_max, int32_t groups, int64_t ld,
-                                                         double* __restrict__ xi) {
+                                                         const double* __restrict__ W, int32_t n_mock, int32_t n_sub,
+                                                         int32_t n_r, int32_t n_mu, int32_t rows_max, int32_t groups,
+                                                         int64_t ld, double* __restrict__ xi) {
 #pragma clang fp contract(off)
     for (int64_t blk = blockIdx.x; blk < int64_t(n_mock) * groups; blk += gridDim.x) {
         const int64_t mk = blk / groups;
@@ -147,10 +148,10 @@ __global__ __launch_bounds__(kXiThreads) void k_xi_split(const unsigned long lon
             const double x = den == 0.0 ? nan : (dd - two_over_m * sdr) / den + 1.0;
             out[o] = x;
             xs[t] = x;
-    }
-    __syncthreads();
-    xi_multipoles<1>(xs, ws, rows, k0, n_r, n_mu, 0, out);
-    __syncthreads();
+        }
+        __syncthreads();
+        xi_multipoles<1>(xs, ws, rows, k0, n_r, n_mu, 0, out);
+        __syncthreads();
     }
 }
 
