@@ -25,6 +25,16 @@ def env():
     return torch, lc
 
 
+@pytest.fixture(autouse=True)
+def give_back(env):
+    """The tests hold most of the card's memory at times: none of it stays."""
+    torch, lc = env
+    yield
+    torch.cuda.synchronize()
+    lc.lc_release_caches()
+    torch.cuda.empty_cache()
+
+
 @pytest.fixture(scope="module")
 def counting(env):
     """A batch whose count holds the card for some 80 ms."""
