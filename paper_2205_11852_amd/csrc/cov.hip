@@ -491,6 +491,7 @@ __global__ __launch_bounds__(64) void k_potrf_panel(double* __restrict__ W, int6
     bool bad = false;
 #pragma unroll
     for (int j = 0; j < kNB; j++) {
+        if (!FULL && j >= nb) continue;  // (identity)
         const double d = readlane_f64(r[j], j);
         bad |= !(d > 0.0);
         const double s = sqrt(d);
