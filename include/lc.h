@@ -126,8 +126,11 @@ typedef struct {
 lc_status lc_build_cells(const int32_t* xyz, int64_t n_total, const int64_t* cat_offsets,
                          int32_t n_cat, const lc_binning* b, const lc_mesh_opts* opts,
                          void* stream, lc_cells** out);
-/* Free a mesh once no queued work uses it; also drops the pair-count graphs
- * (LC_GRAPH) captured on it.  NULL is ignored. */
+/* Free a mesh once no queued work uses it (the call waits for the device);
+ * also drops the pair-count graphs (LC_GRAPH) captured on it.  Its memory goes
+ * to the cache of the library's buffers, which keeps at most a sixteenth of the
+ * device's memory until lc_release_caches; what is beyond goes back to the
+ * device.  NULL is ignored. */
 void lc_free_cells(lc_cells* cells);
 
 /* Mesh facts (HOST): grid cells per axis, cell side in units, points. */
@@ -500,9 +503,10 @@ lc_status lc_autotune(const int32_t* xyz, int64_t n_total, const int64_t* cat_of
                       const lc_binning* b, const lc_task* tasks, int32_t n_tasks, int32_t sample_tasks,
                       void* stream, lc_autotune_result* out);
 
-/* Release cached device buffers, graphs, autotuning results and pinned
- * staging memory of the current device (they are otherwise kept until the
- * process ends). */
+/* Release cached device buffers (scratch and the memory of freed meshes, at
+ * most a sixteenth of the device's memory), graphs, autotuning results and
+ * pinned staging memory of the current device (they are otherwise kept until
+ * the process ends). */
 void lc_release_caches(void);
 
 #ifdef __cplusplus
