@@ -17,6 +17,7 @@
 #include <cfloat>
 #include <chrono>
 #include <cmath>
+#include <new>
 #include <vector>
 
 #include "lc_internal.hpp"
@@ -1314,7 +1315,11 @@ class ResidentBlocks {
     bool take(int n, std::chrono::microseconds wait) {
         std::unique_lock<std::mutex> lk(ctx_->resident_mu);
         std::list<const ResidentBlocks*>& line = ctx_->resident_line;
-        line.push_back(this);
+        try {
+            line.push_back(this);
+        } catch (const std::bad_alloc&) {
+            return false;  // (the columns need no place in line)
+        }
         const bool got = ctx_->resident_cv.wait_for(
             lk, wait, [&] { return line.front() == this && ctx_->resident_blocks + n <= ctx_->n_cu; });
         line.remove(this);
